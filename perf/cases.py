@@ -253,3 +253,37 @@ def tolerance(case):
         # four times the distance to the same formulas in float64 (2.5e-7, single values 1.2e-6)
         return {"rel": 1e-6, "max": 5e-6, "differ": 0.0}
     return "exact"                                     # indices and copied rows
+
+
+def _float32(x):
+    return float(np.float32(x))
+
+
+def exact(case, seed):
+    """The scores of the stand-alone entry points in float64; indices and copied rows have no such value."""
+    if case["op"] != "staged":
+        return None
+    state = prepare(case, seed)
+    k_all, q_all = state["k"], state["q"]
+    H, G, a, W, n = case["kv_heads"], case["group"], case["alpha"], case["pool_w"], case["n_tokens"] - case["alpha"]
+    out = {name: torch.empty(k_all.shape[:2] + (n,), dtype=torch.float64, device="cuda") for name in ("importance", "redundancy", "mean_sim")}
+    later = torch.arange(1, n + 1, device="cuda")
+    for p in range(k_all.shape[0]):
+        for h in range(H):
+            k = k_all[p, h, :n].double()
+            logits = (q_all[p, h * G:(h + 1) * G].double().reshape(G * a, D) @ k.t() / math.sqrt(D)).reshape(G, a, n)
+            weights = torch.softmax(logits.amax(0), -1)
+            padded = torch.nn.functional.pad(weights, (W, W - 1))              # weights are positive: zeros change no maximum
+            out["importance"][p, h] = padded.unfold(-1, 2 * W, 1).amax(-1).mean(0)
+            unit = k / (k.norm(dim=-1, keepdim=True) + 1e-8)
+            sim = unit @ unit.t()
+            sim.fill_diagonal_(0.0)
+            # each token's similarity to its most recent partner above T does not count
+            last = ((sim > _float32(case["T"])) * later).amax(-1)
+            forgiven = torch.where(last > 0, sim.gather(-1, (last - 1).clamp_min(0)[:, None])[:, 0], 0.0)
+            mean = (sim.sum(-1) - forgiven) / n
+            out["mean_sim"][p, h] = mean
+            out["redundancy"][p, h] = torch.softmax(mean, -1)
+    lam = _float32(case["lam"])
+    out["score"] = lam * out["importance"] - (1.0 - lam) * out["redundancy"]
+    return dict(importance=out["importance"], redundancy=out["redundancy"], mean_sim=out["mean_sim"], score=out["score"], kept=None, k=None, v=None)
