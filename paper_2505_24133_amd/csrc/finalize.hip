@@ -40,11 +40,11 @@ struct FinArgs {
   float* z_tmp;          // [heads][n_pad] scores for the shared selection, or nullptr
   int32_t* kept;         // [heads][budget]
   int n, n_pad, stat_groups, alpha, W, k_sel, budget, pool_floats, pool_rows;
-  // similarity rows whose column scan was split over several workgroups: per-part hit counts and
-  // running sums, merged here (most recent part first) before the softmax
+  // similarity rows whose column scan was split over several workgroups: what each part found, merged here
+  // (the most recent part that found something) before the softmax
   const float* rnorm;    // [heads][n_pad]
-  const int* part_cnt;   // [heads][parts][n_pad]
-  const float* part_pre; // [heads][parts][n_pad]
+  const int* part_cnt;   // [heads][n_pad]          triangular scan: whether an older partner was met
+  const float* part_pre; // [heads][parts][n_pad]   similarity to the partner, 0 if there is none
   int parts;
   const unsigned long long* newer;   // [heads][n_pad] or nullptr: triangular scan, most recent newer partner per token
   int pool_after_mean;
@@ -189,14 +189,15 @@ __global__ __launch_bounds__(kFinThreads, PLAIN == 2 ? 8 : 4) void finalize_kern
   const int lane = t & 63;
   const int head = blockIdx.x;
   const int n = a.n;
-  // PLAIN == 2 additionally fixes the paper's window sizes, alpha = 8 and W = 4, at compile time
-  const int alpha = (PLAIN == 2) ? 8 : a.alpha;
-  const int W = (PLAIN == 2) ? 4 : a.W;
+  // PLAIN == 2 additionally fixes the paper's window sizes, alpha = 8 and W = 4, at compile time; PLAIN == 3 is the
+  // same for a split similarity pass (few heads, so without the bound on registers)
+  const int alpha = (PLAIN >= 2) ? 8 : a.alpha;
+  const int W = (PLAIN >= 2) ? 4 : a.W;
   const int qrows = PLAIN ? alpha : a.rows;
   const int pool_rows = PLAIN ? alpha : a.pool_rows;
   const int group_mode = PLAIN ? 0 : a.group_mode;
   const bool pool_after_mean = PLAIN ? false : a.pool_after_mean != 0;
-  const int sim_parts = PLAIN ? 1 : a.parts;
+  const int sim_parts = (PLAIN == 1 || PLAIN == 2) ? 1 : a.parts;
   const unsigned long long* credit = PLAIN ? nullptr : a.credit;
   const unsigned long long* newer = PLAIN ? nullptr : a.newer;
   const float* lg = a.logit + (int64_t)head * qrows * a.n_pad;
@@ -228,14 +229,16 @@ __global__ __launch_bounds__(kFinThreads, PLAIN == 2 ? 8 : 4) void finalize_kern
       // beta = 1 (the only case that is split): the most recent column part that found a hit supplies
       // the forgiven similarity; the slot holds the closed form until now
       for (int i = t; i < n; i += kFinThreads) {
+        // (a hit's similarity exceeds T >= 0, so 0 says that the part found none; all parts' reports are requested at
+        // once: asked one after the other, most recent first, they cost a memory latency each, up to nine for
+        // one layer of the 8B shape)
+        const float* pre = a.part_pre + (int64_t)head * sim_parts * a.n_pad + i;
+        float x[kGramMaxParts];
+#pragma unroll
+        for (int p = 0; p < kGramMaxParts; ++p) x[p] = pre[(int64_t)min(p, sim_parts - 1) * a.n_pad];
         float forgiven = 0.f;
-        for (int p = sim_parts - 1; p >= 0; --p) {
-          const int64_t at = ((int64_t)head * sim_parts + p) * a.n_pad + i;
-          if (a.part_cnt[at] > 0) {
-            forgiven = a.part_pre[at];
-            break;
-          }
-        }
+#pragma unroll
+        for (int p = 0; p < kGramMaxParts; ++p) forgiven = (x[p] != 0.f) ? x[p] : forgiven;
         sb[i] = mean_sim_finish(sb[i], a.rnorm[(int64_t)head * a.n_pad + i], forgiven, n);
       }
     }
@@ -532,14 +535,19 @@ hipError_t launch_finalize(const Plan& pl, int mode, char* ws,
   // the instantiations without the variants' branches serve the default readings with W a positive
   // multiple of two (other shapes and flags take the general one; only the fused modes are doubled)
   const bool plain_imp = pl.gqa_mode == 0 && !pl.pool_after_mean && pl.W > 0 && (pl.W & 1) == 0;
-  const bool plain_red = pl.gram_parts == 1 && !pl.recency_transposed && !pl.triangular;
+  const bool default_rule = !pl.recency_transposed && !pl.triangular;
+  const bool plain_red = pl.gram_parts == 1 && default_rule;
   const bool paper_window = pl.alpha == 8 && pl.W == 4;
   if (plain_imp && plain_red && mode == (kModeImportance | kModeRedundancy | kModeSelect)) {
     if (paper_window) return launch_plain<kModeImportance | kModeRedundancy | kModeSelect, 2>(a, pl.heads, lds, stream);
     return launch_plain<kModeImportance | kModeRedundancy | kModeSelect, 1>(a, pl.heads, lds, stream);
   }
+  if (plain_imp && paper_window && default_rule && pl.gram_parts > 1 && mode == (kModeImportance | kModeRedundancy | kModeSelect))
+    return launch_plain<kModeImportance | kModeRedundancy | kModeSelect, 3>(a, pl.heads, lds, stream);
   if (plain_imp && paper_window && mode == (kModeImportance | kModeSelect))       // attention-only eviction
     return launch_plain<kModeImportance | kModeSelect, 2>(a, pl.heads, lds, stream);
+  if (plain_imp && paper_window && mode == kModeImportance)                       // the stand-alone importance score
+    return launch_plain<kModeImportance, 2>(a, pl.heads, lds, stream);
   switch (mode) {
     case kModeImportance: return launch_mode<kModeImportance>(a, pl.heads, lds, stream);
     case kModeRedundancy: return launch_mode<kModeRedundancy>(a, pl.heads, lds, stream);
