@@ -61,7 +61,8 @@ typedef enum {
  * `beta` most recent similar tokens have been found cannot change any more (Sec. 3.3 zeroes only those
  * beta entries), so rows in that state take no further part in the pass and the rows still open are
  * gathered into fewer waves as their number falls.  Results are bit-identical to flags = 0; only the
- * amount of matrix work differs (data dependent).
+ * amount of matrix work differs (data dependent).  With beta = 1 and T <= 0.9 the default schedule leaves such
+ * rows out by itself (unless the pass is split for few heads) and the flag changes nothing.
  */
 #define RKV_FLAG_SKIP_SATURATED 1u
 /*

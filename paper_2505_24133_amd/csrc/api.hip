@@ -148,7 +148,7 @@ rkv_status make_plan(const rkv_params* prm, Plan* pl) {
   pl->off_stats = take(heads * pl->chunks * 4 * pl->qrows * 2 * 4);
   pl->off_sbar = take(heads * np * 4);
   pl->off_imp = take(heads * np * 4);
-  pl->off_red = take(heads * np * 4);
+  pl->off_open = take(heads * np * 4);
   pl->off_z = take(heads * np * 4);
   pl->off_credit = take(pl->recency_transposed || pl->triangular ? heads * np * 8 : 0);
   const size_t parts = (size_t)parts_reserved;

@@ -39,6 +39,7 @@ struct GramArgs {
   unsigned long long* credit;   // [heads][n_pad] or nullptr: forgiven similarities charged to the partner
   int* part_cnt;                // [heads][parts][n_pad] hits per row found by one column part
   float* part_pre;              // [heads][parts][n_pad] their sum
+  unsigned char* open;          // [heads][4 n_pad] rows handed to the tail kernel (OpenRows), or nullptr
   int H, heads, n, n_pad, chunks, beta;
   int row_blocks, parts;        // workgroups per head = row_blocks * parts
   int64_t ksp, ksh, kst;
@@ -80,14 +81,36 @@ enum GramVariant : int { kPlain = 0, kSplit = 1, kTransposed = 2, kTriangular = 
 // leaves the scan, and when the rows still open fit into half as many row tiles as are in use they are
 // gathered into the first waves (one row tile each) and the other waves only help copying tiles.
 
+// HANDOVER (the default readings, one workgroup per row block): most rows meet their most recent partner within the
+// first tiles, and streaming all older keys through every workgroup for the last few is what a full scan spends
+// its time on.  Once no more than 1 / kHandoverShare of a block's rows are open, the block appends them to the head's list
+// and ends; gram_tail_kernel takes the listed rows, 128 at a time, against the keys that are left.
+// Measured, us, full scan -> hand-over kernel + tail: 256 heads of n = 1144 82 -> 27 + 16, of n = 4216 869 -> 89 + 96; 6144 heads
+// of n = 2168 5824 -> 899 + 607.  A quarter: a tail row costs about four times a row that stays (its group of 128 streams
+// the keys for itself), and below that the list is short.
+constexpr int kHandoverShare = 4;
+// The list of a head: row indices (16 bits: n < 32768), and behind them how many there are and how many of the
+// oldest keys some row of the list has yet to be compared with (a row may meet keys again that it was compared with:
+// none of them was a hit).  Which block's rows come first is a matter of chance and changes no result.
+struct OpenRows {
+  static __device__ __forceinline__ uint16_t* rows(unsigned char* open, int head, int n_pad) {
+    return reinterpret_cast<uint16_t*>(open + (int64_t)head * n_pad * 4);
+  }
+  static __device__ __forceinline__ int* state(unsigned char* open, int head, int n_pad) {
+    return reinterpret_cast<int*>(open + (int64_t)head * n_pad * 4 + n_pad * 2);
+  }
+};
+constexpr int kHandoverBytes = 64;              // HANDOVER: open-row counts of the waves, the block's place in the list
+
 constexpr int kCompactBytes = 3072;             // SKIP: open-row counts of the waves and the records of moved rows
 
-template <int NW, int RT, int TC, int WPS, int VARIANT, bool SKIP, bool B1>
+template <int NW, int RT, int TC, int WPS, int VARIANT, bool SKIP, bool B1, bool HANDOVER>
 __global__ __launch_bounds__(NW * 64, WPS) void gram_kernel(GramArgs a) {
   // WPS = waves per SIMD the register budget is cut for.  With two row tiles per wave there is room for two
   // sets of key fragments and r_j (the next subtile's are fetched a step ahead); with three row tiles (or
   // three waves per SIMD) one set is kept and refilled fragment by fragment behind the subtile's last chain.
   constexpr int KB = (WPS >= 3 || RT >= 3) ? 1 : 2;
+  static_assert(!HANDOVER || (VARIANT == kPlain && B1 && !SKIP), "");
   constexpr int NT = NW * 64;
   constexpr int BM = NW * RT * 32;
   constexpr int NS = TC / 32;                       // 32-key subtiles per tile
@@ -95,12 +118,14 @@ __global__ __launch_bounds__(NW * 64, WPS) void gram_kernel(GramArgs a) {
   static_assert(NW == 2 || NW == 4, "the DMA split assumes 2 or 4 waves");
   static_assert(RT >= 2, "the r_j prefetch needs at least two row tiles per wave");
   static_assert(LOADS % NW == 0, "tile rows must split evenly over the waves");
-  // LDS map: [pseudo-keys | tile 0 | tile 1 | r_j of tile 0 | r_j of tile 1 | SKIP: counts, row records]
+  // LDS map: [pseudo-keys | tile 0 | tile 1 | r_j of tile 0 | r_j of tile 1 | u | SKIP: counts, row records]
   constexpr int OFF_TILE = kPseudoBytes;
   constexpr int TILE_SPAN = LOADS * 1024;            // bytes the DMA copies of one tile cover
   constexpr int OFF_RJ = OFF_TILE + 2 * TILE_SPAN;
-  constexpr int OFF_CNT = OFF_RJ + 2 * TC * 4;       // two sets of NW open-row counts (by iteration parity)
+  constexpr int OFF_U = OFF_RJ + 2 * TC * 4;         // prologue: partial sums of u, one float per thread
+  constexpr int OFF_CNT = OFF_U + NT * 4;            // two sets of NW open-row counts (by iteration parity)
   constexpr int OFF_REC = OFF_CNT + 64;              // NW * 32 records of 5 words
+  constexpr int OFF_BASE = OFF_CNT + 2 * NW * 4;     // HANDOVER: the block's first place in the head's list
   static_assert(64 + NW * 32 * 20 <= kCompactBytes && 2 * NW * 4 <= 64, "record area");
 
   // Workgroups are dealt round-robin to the 8 XCDs; give every XCD whole heads so that a head's
@@ -197,11 +222,24 @@ __global__ __launch_bounds__(NW * 64, WPS) void gram_kernel(GramArgs a) {
   const int nct = ct_hi - ct_lo;
   const bool split = parts > 1 || VARIANT == kTriangular;   // rows report to the finalize kernel instead of closing their sum
   const bool closing = part == parts - 1;           // the part that also writes the closed-form row sums
-  if (nct > 0) issue_tile(ct_hi - 1, 0);
 
-  // ---- prologue: u -> three bf16 pseudo-keys, the wave's rows -> registers.  Every global load of
-  // the prologue is issued before anything waits for one of them (one memory latency, not four):
-  // rows past n read row n - 1 (their results are never written and their threshold is +inf).
+  // ---- prologue: u -> three bf16 pseudo-keys, the wave's rows -> registers.  The rows travel through the
+  // tile buffers, 32 of the wave's in its quarter of each (whole rows a copy: read as fragments straight from
+  // memory they cost four times the address cycles, 64 cache lines an instruction: 6144 heads of n = 2168 987 -> 900 us);
+  // the first two row tiles come with the loads for u in one memory latency, the third with the first key tile.
+  // Rows past n read row n - 1 (their results are never written and their threshold is +inf).
+  // (Where the scan is known to be long the fragments are still read directly: their address cycles overlap with the
+  // other workgroup's scan, and the copies' second memory latency does not pay: 1 us of 155 for one sequence at T = 0.95.)
+  constexpr bool STAGED_ROWS = HANDOVER || VARIANT == kSplit;
+  static_assert(NW * 32 <= TC && RT <= 3, "a row tile of every wave fits a tile buffer");
+  auto copy_row_tile = [&](int rt, int buf) {
+#pragma unroll
+    for (int jj = 0; jj < 8; ++jj) {
+      const int at = jj * 4 + (lane >> 4);
+      dma16(kbase, (uint32_t)min(tile_row0(rt) + at, n - 1) * row_bytes + (uint32_t)((lane & 15) ^ (at & 15)) * 16u,
+            lds0 + (uint32_t)(OFF_TILE + buf * TILE_SPAN + jj * 4 * kRowBytes) + (uint32_t)(wave_s * 32 * kRowBytes));
+    }
+  };
   bf16x8 res[RT][8];
   float thr[RT], sub[RT], rowdot[RT], rni[RT];
   int cnt[RT];
@@ -210,21 +248,34 @@ __global__ __launch_bounds__(NW * 64, WPS) void gram_kernel(GramArgs a) {
     if constexpr (SKIP) return rowid[rt];
     else return tile_row0(rt) + lrow;
   };
+  auto read_row_tile = [&](int rt, int buf) {
+#pragma unroll
+    for (int kk = 0; kk < 8; ++kk)
+      res[rt][kk] = *reinterpret_cast<const bf16x8*>(gram_lds + OFF_TILE + buf * TILE_SPAN + slot_offset(wave * 32 + lrow, kk * 2 + half));
+  };
+  if constexpr (STAGED_ROWS) {
+    copy_row_tile(0, 0);
+    if (rte > 1) copy_row_tile(1, 1);
+  } else {
+    if (nct > 0) issue_tile(ct_hi - 1, 0);
+  }
 #pragma unroll
   for (int rt = 0; rt < RT; ++rt) {
     const int rowc = min(tile_row0(rt) + lrow, n - 1);
     rni[rt] = rn[rowc];
+    if constexpr (!STAGED_ROWS) {
 #pragma unroll
-    for (int kk = 0; kk < 8; ++kk) {
-      const uint4 x = *reinterpret_cast<const uint4*>(kbase + (int64_t)rowc * a.kst + kk * 16 + half * 8);
-      __builtin_memcpy(&res[rt][kk], &x, 16);
+      for (int kk = 0; kk < 8; ++kk) {
+        const uint4 x = *reinterpret_cast<const uint4*>(kbase + (int64_t)rowc * a.kst + kk * 16 + half * 8);
+        __builtin_memcpy(&res[rt][kk], &x, 16);
+      }
     }
   }
   {
     // u = sum of the pre-pass's per-chunk partials, in a fixed order; all threads load in parallel,
     // eight chunks per thread in flight
     constexpr int GROUPS = NT / kHeadDim;
-    float* ured = reinterpret_cast<float*>(gram_lds + OFF_TILE + TILE_SPAN);   // tile 1 is not in use yet
+    float* ured = reinterpret_cast<float*>(gram_lds + OFF_U);
     const int e = t & (kHeadDim - 1), grp = t >> 7;
     const float* up = a.upart + (int64_t)head * a.chunks * kHeadDim + e;
     float usum = 0.f;
@@ -247,10 +298,24 @@ __global__ __launch_bounds__(NW * 64, WPS) void gram_kernel(GramArgs a) {
     rowdot[rt] = 0.f;
     rowid[rt] = row < n ? row : -1;
   }
+  // (a wave's reads of a buffer have returned before anything is copied over it: its own reads here, every
+  // wave's behind the barriers)
+  if constexpr (STAGED_ROWS) {
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    read_row_tile(0, 0);
+    read_row_tile(1, 1);
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    if constexpr (RT == 3) {
+      if (rte > 2) copy_row_tile(2, 1);
+    }
+  }
   __syncthreads();
+  if constexpr (STAGED_ROWS) {
+    if (nct > 0) issue_tile(ct_hi - 1, 0);
+  }
   if (t < kHeadDim) {
     constexpr int GROUPS = NT / kHeadDim;
-    const float* ured = reinterpret_cast<const float*>(gram_lds + OFF_TILE + TILE_SPAN);
+    const float* ured = reinterpret_cast<const float*>(gram_lds + OFF_U);
     float u = ured[t];
 #pragma unroll
     for (int g = 1; g < GROUPS; ++g) u += ured[t + g * kHeadDim];
@@ -264,6 +329,10 @@ __global__ __launch_bounds__(NW * 64, WPS) void gram_kernel(GramArgs a) {
     }
   }
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  if constexpr (STAGED_ROWS && RT == 3) {
+    read_row_tile(2, 1);
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+  }
   __syncthreads();
 
   // 16-byte A-operand fragments of subtile s: key row lane%32, k-slice (kk, lane/32)
@@ -481,7 +550,7 @@ __global__ __launch_bounds__(NW * 64, WPS) void gram_kernel(GramArgs a) {
       } else {
         // the finalize kernel finishes the mean once every part has reported its hit (beta = 1: the most
         // recent part that found one supplies it); until then the slot holds the closed form
-        a.part_cnt[((int64_t)head * parts + part) * a.n_pad + row] = cnt[rt];
+        if constexpr (VARIANT == kTriangular) a.part_cnt[(int64_t)head * a.n_pad + row] = cnt[rt];
         a.part_pre[((int64_t)head * parts + part) * a.n_pad + row] = sub[rt];
         if (closing) a.sbar[(int64_t)head * a.n_pad + row] = closed;
       }
@@ -491,6 +560,7 @@ __global__ __launch_bounds__(NW * 64, WPS) void gram_kernel(GramArgs a) {
   // ---- stream the tiles, most recent first, from iteration it0 on; RTE = row tiles of the wave that take
   // part (RT, or 1 in a narrow row block and after open rows have been gathered).  Returns the iteration
   // to go on with in the one-row-tile form, or nct when the scan is over.
+  int stop_ct = -1, stop_total = 0, stop_before = 0;   // HANDOVER: last tile scanned, open rows of the block and of the waves before this one
   int tiles_now = NW * rte;                            // SKIP: row tiles of the workgroup that may hold open rows
   auto scan = [&](auto rte, int it0) __attribute__((always_inline)) -> int {
   constexpr int RTE = decltype(rte)::value;
@@ -582,7 +652,33 @@ __global__ __launch_bounds__(NW * 64, WPS) void gram_kernel(GramArgs a) {
     }
 
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    if constexpr (!SKIP) {
+    if constexpr (HANDOVER) {
+      // Looked at after tiles 1, 2, 4, 8 and then every eighth: counting costs a wave ~100 cycles of the ~9000 of a tile.
+      const bool look = ((it & (it + 1)) == 0 || (it & 7) == 7) && it + 1 < nct;
+      int* cbuf = reinterpret_cast<int*>(gram_lds + OFF_CNT) + (it & 1) * NW;
+      if (look) {
+        int mine = 0;
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt) mine += __popcll(__ballot(half == 0 && thr[rt] != INFINITY));
+        if (lane == 0) cbuf[wave_s] = mine;
+      }
+      __syncthreads();
+      if (look) {
+        int total = 0, before = 0;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) {
+          const int c = __builtin_amdgcn_readfirstlane(cbuf[w]);
+          total += c;
+          before += (w < wave_s) ? c : 0;
+        }
+        if (total * kHandoverShare <= min(BM, n - rb * BM)) {
+          stop_ct = ct;
+          stop_total = total;
+          stop_before = before;
+          return nct;
+        }
+      }
+    } else if constexpr (!SKIP) {
       __syncthreads();
     } else {
       // open rows of this wave, per row tile (one lane of each row's pair counts)
@@ -665,26 +761,220 @@ __global__ __launch_bounds__(NW * 64, WPS) void gram_kernel(GramArgs a) {
   }
 
   // ---- closed-form row sums minus the forgiven similarities
+  if constexpr (HANDOVER) {
+    if (stop_total > 0) {
+      // the rows still open leave for the tail kernel, which goes on below the last tile scanned: a row's
+      // closed form and its index
+      int* base = reinterpret_cast<int*>(gram_lds + OFF_BASE);
+      if (t == 0) {
+        int* state = OpenRows::state(a.open, head, a.n_pad);
+        *base = atomicAdd(state, stop_total);
+        atomicMax(state + 1, stop_ct * TC);
+      }
+      __syncthreads();
+      uint16_t* list = OpenRows::rows(a.open, head, a.n_pad);
+      int slot = *base + stop_before;
+#pragma unroll
+      for (int rt = 0; rt < RT; ++rt) {
+        const bool open = half == 0 && thr[rt] != INFINITY;
+        const unsigned long long ob = __ballot(open);
+        if (open) {
+          const int row = row_of(rt);
+          list[slot + __popcll(ob & ((1ull << lane) - 1ull))] = (uint16_t)row;
+          a.sbar[(int64_t)head * a.n_pad + row] = mean_sim_closed(rni[rt], rowdot[rt], a.eps);
+        } else if (half == 0) {
+          emit(rt);
+        }
+        slot += __popcll(ob);
+      }
+      return;
+    }
+  }
   if (half == 0) {
 #pragma unroll
     for (int rt = 0; rt < RT; ++rt) emit(rt);
   }
 }
 
-template <int NW, int RT, int TC, int WPS, int VARIANT, bool SKIP, bool B1 = false>
+// The rows of a head that were still open when their row block left the scan, 128 at a time against all older keys.
+// Every wave of the workgroup holds the same rows (up to four row tiles, MFMA B operand) and takes every NW-th subtile of
+// 32 keys, most recent first, through two LDS buffers of its own: the next subtile's copies are in flight while one
+// is used, no barrier stands in the scan, and the copies are whole rows (fragments read straight from memory touch a
+// quarter of each cache line at a time and ran at a quarter of this kernel's rate).  A row is done when a
+// subtile more recent than those a wave still has to look at has met a hit (a maximum of key << 32 | value in LDS).
+// The products are summed in the same order as in gram_kernel, so a row's result does not depend on who found it.
+// Measured on 6144 heads of n = 2168 (about 100 rows a head): 607 us, 5.6 TB/s of keys; 64 rows a group 920, fragments from
+// memory 1785.  Bound: the keys, once per 128 rows; eight waves (64 KB of copies in flight) on a compute unit.
+constexpr int kTailTiles = 4;
+constexpr int kTailRows = kTailTiles * 32;
+constexpr int kTailSpan = 32 * kRowBytes + 256;          // one subtile's keys and r_j
+template <int NW>
+__global__ __launch_bounds__(NW * 64, 2) void gram_tail_kernel(GramArgs a, int groups) {
+  __shared__ unsigned long long best[kTailRows];
+  const int xcd = blockIdx.x & 7;
+  const int q = blockIdx.x >> 3;
+  const int head = (q / groups) * 8 + xcd;               // a head's groups stream the same keys at the same time
+  if (head >= a.heads) return;
+  const int* state = OpenRows::state(a.open, head, a.n_pad);
+  const int count = state[0], subtiles = state[1] >> 5;
+  const uint16_t* list = OpenRows::rows(a.open, head, a.n_pad);
+  const int t = threadIdx.x;
+  const int lane = t & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int lrow = lane & 31;
+  const int half = lane >> 5;
+  const int p = head / a.H;
+  const uint16_t* kbase = a.k + p * a.ksp + (head - p * a.H) * a.ksh;
+  const float* rn = a.rnorm + (int64_t)head * a.n_pad;
+  float* sbar = a.sbar + (int64_t)head * a.n_pad;
+  const uint32_t lds0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(uintptr_t)gram_lds) + wave * 2 * kTailSpan;
+  const unsigned char* mine = gram_lds + wave * 2 * kTailSpan;
+  // Subtile s covers keys 32 s .. 32 s + 31, all older than the tiles gram_kernel has scanned and so below n (and
+  // the 64 r_j fetched from 32 s on lie inside the head's n_pad).  Copy jj moves rows 4 jj .. 4 jj + 3 of it.
+  const uint32_t row_bytes = (uint32_t)a.kst * 2u;
+  static_assert(kTailTiles <= NW, "one wave copies each row tile");
+  auto copy_subtile = [&](int s, int buf) {
+    const uint64_t src = (uint64_t)(uintptr_t)kbase + (uint64_t)(uint32_t)(s * 32) * row_bytes;
+#pragma unroll
+    for (int jj = 0; jj < 8; ++jj) {
+      const int row = jj * 4 + (lane >> 4);
+      dma16(reinterpret_cast<const void*>(src), (uint32_t)row * row_bytes + (uint32_t)((lane & 15) ^ (row & 15)) * 16u,
+            lds0 + (uint32_t)(buf * kTailSpan + jj * 4 * kRowBytes));
+    }
+    dma4(rn + s * 32, (uint32_t)lane * 4u, lds0 + (uint32_t)(buf * kTailSpan + 32 * kRowBytes));
+  };
+  for (int g = q % groups; g * kTailRows < count; g += groups) {
+    if (t < kTailRows) best[t] = 0ull;
+    const int tiles = min((count - g * kTailRows + 31) >> 5, kTailTiles);
+    bf16x8 res[kTailTiles][8];
+    float thr[kTailTiles], r[kTailTiles];
+    int row[kTailTiles];
+    // row tile w is copied by wave w into its first buffer, whole rows at a time, and read there by all; the wave's
+    // first subtile of keys goes to the second buffer meanwhile
+    auto listed = [&](int slot) -> int { return list[min(slot, count - 1)]; };
+    if (wave < tiles) {
+#pragma unroll
+      for (int jj = 0; jj < 8; ++jj) {
+        const int at = jj * 4 + (lane >> 4);
+        dma16(kbase, (uint32_t)listed(g * kTailRows + wave * 32 + at) * row_bytes + (uint32_t)((lane & 15) ^ (at & 15)) * 16u,
+              lds0 + (uint32_t)(jj * 4 * kRowBytes));
+      }
+    }
+    int s = subtiles - 1 - wave;
+    if (s >= 0) copy_subtile(s, 1);
+#pragma unroll
+    for (int rt = 0; rt < kTailTiles; ++rt) {
+      const int slot = g * kTailRows + rt * 32 + lrow;
+      row[rt] = listed(slot);
+      r[rt] = rn[row[rt]];
+      thr[rt] = slot < count ? a.T / r[rt] : INFINITY;
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+#pragma unroll
+    for (int rt = 0; rt < kTailTiles; ++rt)
+#pragma unroll
+      for (int kk = 0; kk < 8; ++kk)
+        res[rt][kk] = *reinterpret_cast<const bf16x8*>(gram_lds + rt * 2 * kTailSpan + slot_offset(lrow, kk * 2 + half));
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");     // read before the barrier behind which the buffers are used again
+    __syncthreads();
+    for (int buf = 1; s >= 0; s -= NW, buf ^= 1) {
+      // done: a hit above this subtile (the word holds key + 1 in its upper half)
+      float limit[kTailTiles];
+      bool open = false;
+#pragma unroll
+      for (int rt = 0; rt < kTailTiles; ++rt) {
+        const uint32_t met = (uint32_t)(__hip_atomic_load(&best[rt * 32 + lrow], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) >> 32);
+        limit[rt] = met > (uint32_t)(s * 32 + 32) ? INFINITY : thr[rt];
+        open = open || limit[rt] != INFINITY;
+      }
+      if (!__any(open)) break;
+      copy_subtile(max(s - NW, 0), buf ^ 1);      // the last one is not used
+      asm volatile("s_waitcnt vmcnt(9)" ::: "memory");     // all but the nine copies just issued
+      const unsigned char* tile = mine + buf * kTailSpan;
+      bf16x8 kf[8];
+      float rj[16];
+#pragma unroll
+      for (int kk = 0; kk < 8; ++kk) kf[kk] = *reinterpret_cast<const bf16x8*>(tile + slot_offset(lrow, kk * 2 + half));
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const float4 v = *reinterpret_cast<const float4*>(tile + 32 * kRowBytes + (i * 8 + half * 4) * 4);
+        rj[4 * i] = v.x; rj[4 * i + 1] = v.y; rj[4 * i + 2] = v.z; rj[4 * i + 3] = v.w;
+      }
+#pragma unroll
+      for (int rt = 0; rt < kTailTiles; ++rt) {
+        if (rt >= tiles) break;
+        f32x16 acc;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) acc[i] = 0.f;
+#pragma unroll
+        for (int kk = 0; kk < 8; ++kk) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[kk], res[rt][kk], acc, 0, 0, 0);
+        float m = acc[0] * rj[0];
+#pragma unroll
+        for (int i = 1; i < 16; i += 3) m = fmaxf(m, fmaxf(acc[i] * rj[i], fmaxf(acc[i + 1] * rj[i + 1], acc[i + 2] * rj[i + 2])));
+        if (__any(m > limit[rt])) {
+          const int own = row[rt] - s * 32 - 4 * half;     // the row itself, in this lane's numbering, if it is here
+          float val = 0.f;
+          int at = -1;
+#pragma unroll
+          for (int i = 0; i < 16; ++i) {
+            const float v = acc[i] * rj[i];
+            const int key = 8 * (i >> 2) + (i & 3);
+            const bool hit = v > limit[rt] && key != own;
+            val = hit ? v : val;
+            at = hit ? key : at;
+          }
+          // keys differ, so the value's bits never decide the maximum
+          if (at >= 0)
+            atomicMax(&best[rt * 32 + lrow], ((unsigned long long)(uint32_t)(s * 32 + 4 * half + at + 1) << 32) | __float_as_uint(val));
+        }
+      }
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");       // a copy may still be on its way into the buffers
+    __syncthreads();
+    if (wave == 0 && half == 0) {
+#pragma unroll
+      for (int rt = 0; rt < kTailTiles; ++rt)
+        if (g * kTailRows + rt * 32 + lrow < count)
+          sbar[row[rt]] = mean_sim_finish(sbar[row[rt]], r[rt], __uint_as_float((uint32_t)best[rt * 32 + lrow]), a.n);
+    }
+    __syncthreads();
+  }
+}
+
+// Workgroups per head: enough for the machine when there are few heads, and one per 128 rows at most (a row block
+// hands over at most 1 / kHandoverShare of its rows); what is left is taken in turn.  Up to one head per compute
+// unit a head gets eight waves, above that four, and two workgroups share the compute unit.
+template <int NW>
+hipError_t launch_tail_waves(const GramArgs& a, const Plan& pl, hipStream_t stream) {
+  constexpr size_t lds = NW * 2 * kTailSpan;
+  static const hipError_t configured = hipFuncSetAttribute(reinterpret_cast<const void*>(&gram_tail_kernel<NW>),
+                                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  if (configured != hipSuccess) return configured;
+  const int most = pl.n / kHandoverShare / kTailRows + 1;
+  const int groups = std::max(1, std::min(most, (NW == 8 ? 1 : 2) * device_compute_units() / pl.heads));
+  hipLaunchKernelGGL(gram_tail_kernel<NW>, dim3((unsigned)((pl.heads + 7) / 8 * 8 * groups)), dim3(NW * 64), lds, stream, a, groups);
+  return hipGetLastError();
+}
+hipError_t launch_tail(const GramArgs& a, const Plan& pl, hipStream_t stream) {
+  return pl.heads <= device_compute_units() ? launch_tail_waves<8>(a, pl, stream) : launch_tail_waves<4>(a, pl, stream);
+}
+
+template <int NW, int RT, int TC, int WPS, int VARIANT, bool SKIP, bool B1 = false, bool HANDOVER = false>
 hipError_t launch_shape(GramArgs a, const Plan& pl, hipStream_t stream) {
   constexpr int BM = NW * RT * 32;
-  constexpr size_t lds = kPseudoBytes + 2 * (size_t)TC * kRowBytes + 2 * (size_t)TC * 4 + (SKIP ? kCompactBytes : 0);
+  constexpr size_t lds = kPseudoBytes + 2 * (size_t)TC * kRowBytes + 2 * (size_t)TC * 4 + NW * 64 * 4 +
+                         (SKIP ? kCompactBytes : (HANDOVER ? kHandoverBytes : 0));
   // once per kernel instantiation (initialisation of a function-local static is thread-safe)
   static const hipError_t configured =
-      hipFuncSetAttribute(reinterpret_cast<const void*>(&gram_kernel<NW, RT, TC, WPS, VARIANT, SKIP, B1>),
+      hipFuncSetAttribute(reinterpret_cast<const void*>(&gram_kernel<NW, RT, TC, WPS, VARIANT, SKIP, B1, HANDOVER>),
                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   if (configured != hipSuccess) return configured;
   static_assert(BM == (SKIP ? kGramRowsSkip : kGramRows) && TC == kGramTile, "the plan's split of the similarity pass assumes this shape");
   const int head_groups = (pl.heads + 7) / 8;
   a.row_blocks = (pl.n + BM - 1) / BM;
   const dim3 grid((unsigned)((int64_t)head_groups * 8 * a.row_blocks * a.parts));
-  hipLaunchKernelGGL((gram_kernel<NW, RT, TC, WPS, VARIANT, SKIP, B1>), grid, dim3(NW * 64), lds, stream, a);
+  hipLaunchKernelGGL((gram_kernel<NW, RT, TC, WPS, VARIANT, SKIP, B1, HANDOVER>), grid, dim3(NW * 64), lds, stream, a);
   return hipGetLastError();
 }
 
@@ -708,6 +998,12 @@ hipError_t launch_gram(const Plan& pl, const void* k, char* ws, hipStream_t stre
   a.row_blocks = 0; a.parts = pl.gram_parts;
   a.part_cnt = reinterpret_cast<int*>(ws + pl.off_pcnt);
   a.part_pre = reinterpret_cast<float*>(ws + pl.off_ppre);
+  a.open = handover(pl) ? reinterpret_cast<unsigned char*>(ws + pl.off_open) : nullptr;
+  if (a.open != nullptr) {
+    // (rows that are done are left out here in any case, so RKV_FLAG_SKIP_SATURATED changes nothing)
+    const hipError_t e = launch_shape<4, 3, 128, 2, kPlain, false, true, true>(a, pl, stream);
+    return e != hipSuccess ? e : launch_tail(a, pl, stream);
+  }
   if (pl.skip_saturated) {
     // (two row tiles per wave: the gathering of open rows needs the registers a third one would take)
     if (a.credit != nullptr) return launch_shape<4, 2, 128, 2, kTransposed, true>(a, pl, stream);

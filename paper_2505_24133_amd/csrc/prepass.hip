@@ -24,6 +24,7 @@ struct PrepassArgs {
   const uint16_t* k;
   float* rnorm;
   unsigned long long* credit;   // zeroed here for the similarity pass, or nullptr
+  unsigned char* open;          // [heads][4 n_pad]: the two words behind a head's list of open rows are zeroed here, or nullptr
   float* upart;
   float* logit;
   float* stats;
@@ -169,6 +170,8 @@ __global__ __launch_bounds__(kPrepassThreads, 3) void prepass_kernel(PrepassArgs
     for (int m = 0; m < 8; ++m)
       if (j0 + m * 16 + rbase < a.n) *reinterpret_cast<uint4*>(kd + (int64_t)m * 16 * kHeadDim) = regs[m];
   }
+  if (a.open != nullptr && chunk == 0 && t < 2)
+    reinterpret_cast<int*>(a.open + (int64_t)head * a.n_pad * 4 + a.n_pad * 2)[t] = 0;
   if (c16 == 0) {
     // one lane per row writes r (0 in the padding up to n_pad) and clears the partner counter
     float* rn = a.rnorm + (int64_t)head * a.n_pad + j0 + rbase;
@@ -323,6 +326,7 @@ hipError_t launch_prepass(const Plan& pl, const void* q_obs, const void* k, char
   a.rnorm = reinterpret_cast<float*>(ws + pl.off_rnorm);
   a.upart = reinterpret_cast<float*>(ws + pl.off_upart);
   a.credit = (pl.recency_transposed || pl.triangular) ? reinterpret_cast<unsigned long long*>(ws + pl.off_credit) : nullptr;
+  a.open = handover(pl) ? reinterpret_cast<unsigned char*>(ws + pl.off_open) : nullptr;
   a.logit = reinterpret_cast<float*>(ws + pl.off_logit);
   a.stats = reinterpret_cast<float*>(ws + pl.off_stats);
   a.H = pl.H; a.G = pl.G; a.alpha = pl.alpha; a.n = pl.n; a.n_pad = pl.n_pad; a.chunks = pl.chunks;

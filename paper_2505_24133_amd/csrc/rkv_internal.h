@@ -70,7 +70,7 @@ struct Plan {
                       //                                 32 keys (groups = 4 * chunks) on the pre-pass's register path
   size_t off_sbar;    // float [heads][n_pad]           mean similarity
   size_t off_imp;     // float [heads][n_pad]           importance (fused path)
-  size_t off_red;     // float [heads][n_pad]           redundancy (fused path)
+  size_t off_open;    // bytes [heads][4 n_pad]         rows the similarity pass hands to its tail kernel (gram.hip)
   size_t off_z;       // float [heads][n_pad]           per-head scores Z (shared selection)
   size_t off_credit;  // u64   [heads][n_pad]           forgiven similarity charged to the recent partner, in
                       //                                units of 2^-40 (RKV_FLAG_RECENCY_TRANSPOSED), or the most
@@ -83,6 +83,13 @@ struct Plan {
 };
 
 rkv_status make_plan(const rkv_params* prm, Plan* plan);
+// The similarity pass hands its last open rows to a tail kernel: the default direction of the recency rule with
+// beta = 1, one workgroup per row block, T <= 0.9.  Above that only near-copies are partners, too few rows meet one
+// early for a hand-over (repeated text, T = 0.95, n = 1144: 569 rows open after 8 of 9 tiles) and the empty launch would
+// cost 4.6 us (152.5 -> 157 us for one sequence); at T = 0.5 the same sequence goes from 152 to 120 us.
+inline bool handover(const Plan& pl) {
+  return pl.beta == 1 && pl.gram_parts == 1 && !pl.recency_transposed && !pl.triangular && pl.T <= 0.9f;
+}
 int device_compute_units();   // of the current device; cached after the first query
 
 // Kernel launchers (each enqueues on `stream` and returns hipGetLastError()).
