@@ -49,7 +49,8 @@ class DecodeCache:
                              self.length, self.tokens_seen % s.alpha)
         self.length += 1
         self.tokens_seen += 1
-        if rkv.rkv_should_compress(s, self.length):
+        # (what rkv_should_compress answers for a shape that the append has just accepted)
+        if self.length >= s.n_tokens > s.budget:
             self.compress()
             return True
         return False

@@ -8,6 +8,7 @@ from __future__ import annotations
 
 import ctypes
 import os
+import struct
 from dataclasses import dataclass, field
 from typing import Optional, Tuple
 
@@ -51,6 +52,10 @@ class RkvParams(ctypes.Structure):
         ("page_size", ctypes.c_int32), ("table_stride", ctypes.c_int32), ("block_table", ctypes.c_void_p),
         ("k_stride_page", ctypes.c_int64), ("v_stride_page", ctypes.c_int64),
     ]
+
+
+_PACK_PARAMS = struct.Struct("@9i3fI12q2iP2q").pack_into
+assert struct.calcsize("@9i3fI12q2iP2q") == ctypes.sizeof(RkvParams)
 
 
 class RkvError(RuntimeError):
@@ -120,9 +125,19 @@ class Shape:
 
     def params(self, k: Optional[torch.Tensor] = None, v: Optional[torch.Tensor] = None,
                out: Optional[torch.Tensor] = None, q: Optional[torch.Tensor] = None) -> RkvParams:
-        p = RkvParams(self.num_problems, self.kv_heads, self.q_heads, self.n_tokens, self.head_dim, self.alpha,
-                      self.budget, self.pool_w, self.beta, self.sim_threshold, self.lam, self.eps, self.flags,
-                      0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, None, 0, 0)
+        ks = (0, 0, 0) if k is None or self.page_size else k.stride()[:3]
+        vs = (0, 0, 0) if v is None or self.page_size else v.stride()[:3]
+        p = RkvParams()
+        try:
+            # one call for all fields: a third of the time of setting them one by one
+            _PACK_PARAMS(p, 0, self.num_problems, self.kv_heads, self.q_heads, self.n_tokens, self.head_dim, self.alpha,
+                         self.budget, self.pool_w, self.beta, self.sim_threshold, self.lam, self.eps, self.flags,
+                         *ks, *vs, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0)
+        except (struct.error, OverflowError):
+            # values outside the fields' ranges: ctypes wraps them and the library's own checks answer
+            p = RkvParams(self.num_problems, self.kv_heads, self.q_heads, self.n_tokens, self.head_dim, self.alpha,
+                          self.budget, self.pool_w, self.beta, self.sim_threshold, self.lam, self.eps, self.flags,
+                          *ks, *vs)
         if q is not None and not q.is_contiguous():
             p.q_stride_problem, p.q_stride_head, p.q_stride_token = q.stride(0), q.stride(1), q.stride(2)
         if self.page_size:
@@ -141,10 +156,6 @@ class Shape:
             if out is not None and not out.is_contiguous():
                 p.o_stride_problem, p.o_stride_head, p.o_stride_token = out.stride(0), out.stride(1), out.stride(2)
             return p
-        if k is not None:
-            p.k_stride_problem, p.k_stride_head, p.k_stride_token = k.stride(0), k.stride(1), k.stride(2)
-        if v is not None:
-            p.v_stride_problem, p.v_stride_head, p.v_stride_token = v.stride(0), v.stride(1), v.stride(2)
         if out is not None and not out.is_contiguous():
             p.o_stride_problem, p.o_stride_head, p.o_stride_token = out.stride(0), out.stride(1), out.stride(2)
         return p
@@ -159,7 +170,7 @@ def _ptr(t: Optional[torch.Tensor]) -> Optional[int]:
 
 
 def _stream() -> int:
-    return torch.cuda.current_stream().cuda_stream
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())      # without a Stream object around it
 
 
 def _need_gpu(*tensors: torch.Tensor) -> None:
@@ -175,13 +186,13 @@ def _check_kv(shape: Shape, t: torch.Tensor, what: str) -> None:
             raise ValueError(f"{what} must be a bf16 page pool [pages, {shape.kv_heads}, {shape.page_size}, {shape.head_dim}]")
         return
     want = (shape.num_problems, shape.kv_heads, shape.n_tokens, shape.head_dim)
-    if tuple(t.shape) != want or t.dtype != torch.bfloat16 or t.stride(3) != 1:
+    if t.shape != want or t.dtype != torch.bfloat16 or t.stride(3) != 1:
         raise ValueError(f"{what} must be bf16 {want} with a contiguous last dimension, got {tuple(t.shape)} {t.dtype}")
 
 
 def _check_q(shape: Shape, q: torch.Tensor) -> None:
     want = (shape.num_problems, shape.q_heads, shape.alpha, shape.head_dim)
-    if tuple(q.shape) != want or q.dtype != torch.bfloat16 or q.stride(3) != 1:
+    if q.shape != want or q.dtype != torch.bfloat16 or q.stride(3) != 1:
         raise ValueError(f"q_obs must be bf16 {want} with a contiguous last dimension")
 
 
@@ -206,6 +217,25 @@ def rkv_should_compress(shape: Shape, cached_tokens: int) -> bool:
 def rkv_cache_append(shape: Shape, k_cache: torch.Tensor, v_cache: torch.Tensor, q_cache: torch.Tensor,
                      k_new: torch.Tensor, v_new: torch.Tensor, q_new: torch.Tensor, position: int, q_slot: int) -> None:
     """Write one decoded token's key/value rows at `position` and its query state into slot `q_slot`."""
+    P, H, Hq, d = shape.num_problems, shape.kv_heads, shape.q_heads, shape.head_dim
+    kv, bf16 = (P, H, d), torch.bfloat16
+    # called once per decoded token: everything is asked in one expression, and only where it does not hold are
+    # the checks gone through one by one, to say which
+    if not (not shape.page_size and k_cache.shape == (P, H, shape.n_tokens, d) == v_cache.shape
+            and q_cache.shape == (P, Hq, shape.alpha, d) and k_new.shape == kv == v_new.shape and q_new.shape == (P, Hq, d)
+            and k_cache.dtype is v_cache.dtype is q_cache.dtype is k_new.dtype is v_new.dtype is q_new.dtype is bf16
+            and k_cache.stride(3) == 1 and v_cache.stride(3) == 1 and q_cache.stride(3) == 1
+            and k_new.is_contiguous() and v_new.is_contiguous() and q_new.is_contiguous()
+            and k_cache.is_cuda and v_cache.is_cuda and q_cache.is_cuda and k_new.is_cuda and v_new.is_cuda and q_new.is_cuda):
+        _check_append(shape, k_cache, v_cache, q_cache, k_new, v_new, q_new)
+    prm = shape.params(k_cache, v_cache, q=q_cache)
+    s = load_library().rkv_cache_append(ctypes.byref(prm), k_cache.data_ptr(), v_cache.data_ptr(), q_cache.data_ptr(),
+                                        k_new.data_ptr(), v_new.data_ptr(), q_new.data_ptr(), int(position), int(q_slot), _stream())
+    if s != RKV_OK:
+        raise RkvError(s, "rkv_cache_append")
+
+
+def _check_append(shape: Shape, k_cache, v_cache, q_cache, k_new, v_new, q_new) -> None:
     _need_gpu(k_cache, v_cache, q_cache, k_new, v_new, q_new)
     _check_kv(shape, k_cache, "k_cache")
     _check_kv(shape, v_cache, "v_cache")
@@ -213,13 +243,8 @@ def rkv_cache_append(shape: Shape, k_cache: torch.Tensor, v_cache: torch.Tensor,
     kv = (shape.num_problems, shape.kv_heads, shape.head_dim)
     qs = (shape.num_problems, shape.q_heads, shape.head_dim)
     for t, want in ((k_new, kv), (v_new, kv), (q_new, qs)):
-        if tuple(t.shape) != want or t.dtype != torch.bfloat16 or not t.is_contiguous():
+        if t.shape != want or t.dtype != torch.bfloat16 or not t.is_contiguous():
             raise ValueError(f"new rows must be contiguous bf16 {want}")
-    prm = shape.params(k_cache, v_cache, q=q_cache)
-    s = load_library().rkv_cache_append(ctypes.byref(prm), _ptr(k_cache), _ptr(v_cache), _ptr(q_cache), _ptr(k_new),
-                                        _ptr(v_new), _ptr(q_new), int(position), int(q_slot), _stream())
-    if s != RKV_OK:
-        raise RkvError(s, "rkv_cache_append")
 
 
 def rkv_workspace_size(shape: Shape) -> int:
