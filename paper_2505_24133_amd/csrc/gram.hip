@@ -89,15 +89,16 @@ enum GramVariant : int { kPlain = 0, kSplit = 1, kTransposed = 2, kTriangular = 
 // of n = 2168 5824 -> 899 + 607.  A quarter: a tail row costs about four times a row that stays (its group of 128 streams
 // the keys for itself), and below that the list is short.
 constexpr int kHandoverShare = 4;
-// The list of a head: row indices (16 bits: n < 32768), and behind them how many there are and how many of the
-// oldest keys some row of the list has yet to be compared with (a row may meet keys again that it was compared with:
-// none of them was a hit).  Which block's rows come first is a matter of chance and changes no result.
+// The list of a head: one word per row (the row, and the subtile of 32 keys below which it is still to be compared), and
+// behind n_pad bytes how many there are.  Which block's rows come first is a matter of chance and changes no result.
+// (One restart point for a whole head sent rows that had left late through nearly all keys again: redundancy of 256 heads of
+// n = 4216 whose rows repeat only inside eight segments, a quarter of them nowhere, 1009 us; so 889; full scan 906.)
 struct OpenRows {
-  static __device__ __forceinline__ uint16_t* rows(unsigned char* open, int head, int n_pad) {
-    return reinterpret_cast<uint16_t*>(open + (int64_t)head * n_pad * 4);
+  static __device__ __forceinline__ uint32_t* words(unsigned char* open, int head, int n_pad) {
+    return reinterpret_cast<uint32_t*>(open + (int64_t)head * n_pad * 4);
   }
-  static __device__ __forceinline__ int* state(unsigned char* open, int head, int n_pad) {
-    return reinterpret_cast<int*>(open + (int64_t)head * n_pad * 4 + n_pad * 2);
+  static __device__ __forceinline__ int* count(unsigned char* open, int head, int n_pad) {
+    return reinterpret_cast<int*>(open + (int64_t)head * n_pad * 4 + n_pad);
   }
 };
 constexpr int kHandoverBytes = 64;              // HANDOVER: open-row counts of the waves, the block's place in the list
@@ -763,16 +764,12 @@ __global__ __launch_bounds__(NW * 64, WPS) void gram_kernel(GramArgs a) {
   // ---- closed-form row sums minus the forgiven similarities
   if constexpr (HANDOVER) {
     if (stop_total > 0) {
-      // the rows still open leave for the tail kernel, which goes on below the last tile scanned: a row's
-      // closed form and its index
+      // the rows still open leave for the tail kernel, which goes on below the last tile scanned: a row's closed
+      // form, its index and that tile
       int* base = reinterpret_cast<int*>(gram_lds + OFF_BASE);
-      if (t == 0) {
-        int* state = OpenRows::state(a.open, head, a.n_pad);
-        *base = atomicAdd(state, stop_total);
-        atomicMax(state + 1, stop_ct * TC);
-      }
+      if (t == 0) *base = atomicAdd(OpenRows::count(a.open, head, a.n_pad), stop_total);
       __syncthreads();
-      uint16_t* list = OpenRows::rows(a.open, head, a.n_pad);
+      uint32_t* list = OpenRows::words(a.open, head, a.n_pad);
       int slot = *base + stop_before;
 #pragma unroll
       for (int rt = 0; rt < RT; ++rt) {
@@ -780,7 +777,7 @@ __global__ __launch_bounds__(NW * 64, WPS) void gram_kernel(GramArgs a) {
         const unsigned long long ob = __ballot(open);
         if (open) {
           const int row = row_of(rt);
-          list[slot + __popcll(ob & ((1ull << lane) - 1ull))] = (uint16_t)row;
+          list[slot + __popcll(ob & ((1ull << lane) - 1ull))] = gram_open_word(row, stop_ct * NS);
           a.sbar[(int64_t)head * a.n_pad + row] = mean_sim_closed(rni[rt], rowdot[rt], a.eps);
         } else if (half == 0) {
           emit(rt);
@@ -796,150 +793,167 @@ __global__ __launch_bounds__(NW * 64, WPS) void gram_kernel(GramArgs a) {
   }
 }
 
-// The rows of a head that were still open when their row block left the scan, 128 at a time against all older keys.
-// Every wave of the workgroup holds the same rows (up to four row tiles, MFMA B operand) and takes every NW-th subtile of
-// 32 keys, most recent first, through two LDS buffers of its own: the next subtile's copies are in flight while one
-// is used, no barrier stands in the scan, and the copies are whole rows (fragments read straight from memory touch a
-// quarter of each cache line at a time and ran at a quarter of this kernel's rate).  A row is done when a
-// subtile more recent than those a wave still has to look at has met a hit (a maximum of key << 32 | value in LDS).
-// The products are summed in the same order as in gram_kernel, so a row's result does not depend on who found it.
-// Measured on 6144 heads of n = 2168 (about 100 rows a head): 607 us, 5.6 TB/s of keys; 64 rows a group 920, fragments from
-// memory 1785.  Bound: the keys, once per 128 rows; eight waves (64 KB of copies in flight) on a compute unit.
-constexpr int kTailTiles = 4;
+constexpr int kTailTiles = 4;                            // most row tiles of a group
 constexpr int kTailRows = kTailTiles * 32;
 constexpr int kTailSpan = 32 * kRowBytes + 256;          // one subtile's keys and r_j
-template <int NW>
-__global__ __launch_bounds__(NW * 64, 2) void gram_tail_kernel(GramArgs a, int groups) {
-  __shared__ unsigned long long best[kTailRows];
-  const int xcd = blockIdx.x & 7;
-  const int q = blockIdx.x >> 3;
-  const int head = (q / groups) * 8 + xcd;               // a head's groups stream the same keys at the same time
-  if (head >= a.heads) return;
-  const int* state = OpenRows::state(a.open, head, a.n_pad);
-  const int count = state[0], subtiles = state[1] >> 5;
-  const uint16_t* list = OpenRows::rows(a.open, head, a.n_pad);
-  const int t = threadIdx.x;
+
+// A group of open rows against the older keys, by all NW waves of a workgroup.  Every wave holds the same rows (up to
+// TILES row tiles, MFMA B operand) and takes every NW-th subtile of 32 keys, most recent first, through two LDS buffers of
+// its own: the next subtile's copies are in flight while one is used, no barrier stands in the scan, and the copies are
+// whole rows (fragments read straight from memory touch a quarter of each cache line at a time and ran at a quarter
+// of the rate).  A row is done when a subtile more recent than those a wave still has to look at has met a hit (a
+// maximum of key << 32 | value in LDS); a row tile whose rows are all done is left out.  The products are summed in the
+// same order as in the scan, so a row's result does not depend on who found it.  `words` lists the rows; their
+// closed forms wait in a.sbar.
+// Measured on 6144 heads of n = 2168 (about 100 rows a head): 607 us, 5.6 TB/s of keys; 64 rows a group 920, fragments from
+// memory 1785.  Bound: the keys, once per 128 rows; eight waves (64 KB of copies in flight) on a compute unit.
+template <int NW, int TILES>
+__device__ __forceinline__ void tail_group(const GramArgs& a, int head, const uint16_t* kbase, const uint32_t* words, int rows) {
+  static_assert(TILES <= NW, "one wave copies each row tile");
+  unsigned long long* best = reinterpret_cast<unsigned long long*>(gram_lds + NW * 2 * kTailSpan);
+  int t = threadIdx.x;
+  asm volatile("" : "+v"(t));                            // (addresses formed from it here are not kept, spilled, from the prologue on)
   const int lane = t & 63;
   const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
   const int lrow = lane & 31;
   const int half = lane >> 5;
-  const int p = head / a.H;
-  const uint16_t* kbase = a.k + p * a.ksp + (head - p * a.H) * a.ksh;
   const float* rn = a.rnorm + (int64_t)head * a.n_pad;
   float* sbar = a.sbar + (int64_t)head * a.n_pad;
   const uint32_t lds0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(uintptr_t)gram_lds) + wave * 2 * kTailSpan;
   const unsigned char* mine = gram_lds + wave * 2 * kTailSpan;
-  // Subtile s covers keys 32 s .. 32 s + 31, all older than the tiles gram_kernel has scanned and so below n (and
-  // the 64 r_j fetched from 32 s on lie inside the head's n_pad).  Copy jj moves rows 4 jj .. 4 jj + 3 of it.
   const uint32_t row_bytes = (uint32_t)a.kst * 2u;
-  static_assert(kTailTiles <= NW, "one wave copies each row tile");
+  // Subtile s covers keys 32 s .. 32 s + 31, all below a tile that the scan has seen and so below n (and the 64 r_j
+  // fetched from 32 s on lie inside the head's n_pad).  Copy jj moves rows 4 jj .. 4 jj + 3 of it.
   auto copy_subtile = [&](int s, int buf) {
     const uint64_t src = (uint64_t)(uintptr_t)kbase + (uint64_t)(uint32_t)(s * 32) * row_bytes;
 #pragma unroll
     for (int jj = 0; jj < 8; ++jj) {
-      const int row = jj * 4 + (lane >> 4);
-      dma16(reinterpret_cast<const void*>(src), (uint32_t)row * row_bytes + (uint32_t)((lane & 15) ^ (row & 15)) * 16u,
+      const int at = jj * 4 + (lane >> 4);
+      dma16(reinterpret_cast<const void*>(src), (uint32_t)at * row_bytes + (uint32_t)((lane & 15) ^ (at & 15)) * 16u,
             lds0 + (uint32_t)(buf * kTailSpan + jj * 4 * kRowBytes));
     }
     dma4(rn + s * 32, (uint32_t)lane * 4u, lds0 + (uint32_t)(buf * kTailSpan + 32 * kRowBytes));
   };
-  for (int g = q % groups; g * kTailRows < count; g += groups) {
-    if (t < kTailRows) best[t] = 0ull;
-    const int tiles = min((count - g * kTailRows + 31) >> 5, kTailTiles);
-    bf16x8 res[kTailTiles][8];
-    float thr[kTailTiles], r[kTailTiles];
-    int row[kTailTiles];
-    // row tile w is copied by wave w into its first buffer, whole rows at a time, and read there by all; the wave's
-    // first subtile of keys goes to the second buffer meanwhile
-    auto listed = [&](int slot) -> int { return list[min(slot, count - 1)]; };
-    if (wave < tiles) {
+  if (t < TILES * 32) best[t] = 0ull;
+  const int tiles = (rows + 31) >> 5;
+  bf16x8 res[TILES][8];
+  float thr[TILES], r[TILES];
+  int row[TILES], top = 0;
 #pragma unroll
-      for (int jj = 0; jj < 8; ++jj) {
-        const int at = jj * 4 + (lane >> 4);
-        dma16(kbase, (uint32_t)listed(g * kTailRows + wave * 32 + at) * row_bytes + (uint32_t)((lane & 15) ^ (at & 15)) * 16u,
-              lds0 + (uint32_t)(jj * 4 * kRowBytes));
-      }
-    }
-    int s = subtiles - 1 - wave;
-    if (s >= 0) copy_subtile(s, 1);
-#pragma unroll
-    for (int rt = 0; rt < kTailTiles; ++rt) {
-      const int slot = g * kTailRows + rt * 32 + lrow;
-      row[rt] = listed(slot);
-      r[rt] = rn[row[rt]];
-      thr[rt] = slot < count ? a.T / r[rt] : INFINITY;
-    }
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    __syncthreads();
-#pragma unroll
-    for (int rt = 0; rt < kTailTiles; ++rt)
-#pragma unroll
-      for (int kk = 0; kk < 8; ++kk)
-        res[rt][kk] = *reinterpret_cast<const bf16x8*>(gram_lds + rt * 2 * kTailSpan + slot_offset(lrow, kk * 2 + half));
-    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");     // read before the barrier behind which the buffers are used again
-    __syncthreads();
-    for (int buf = 1; s >= 0; s -= NW, buf ^= 1) {
-      // done: a hit above this subtile (the word holds key + 1 in its upper half)
-      float limit[kTailTiles];
-      bool open = false;
-#pragma unroll
-      for (int rt = 0; rt < kTailTiles; ++rt) {
-        const uint32_t met = (uint32_t)(__hip_atomic_load(&best[rt * 32 + lrow], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) >> 32);
-        limit[rt] = met > (uint32_t)(s * 32 + 32) ? INFINITY : thr[rt];
-        open = open || limit[rt] != INFINITY;
-      }
-      if (!__any(open)) break;
-      copy_subtile(max(s - NW, 0), buf ^ 1);      // the last one is not used
-      asm volatile("s_waitcnt vmcnt(9)" ::: "memory");     // all but the nine copies just issued
-      const unsigned char* tile = mine + buf * kTailSpan;
-      bf16x8 kf[8];
-      float rj[16];
-#pragma unroll
-      for (int kk = 0; kk < 8; ++kk) kf[kk] = *reinterpret_cast<const bf16x8*>(tile + slot_offset(lrow, kk * 2 + half));
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const float4 v = *reinterpret_cast<const float4*>(tile + 32 * kRowBytes + (i * 8 + half * 4) * 4);
-        rj[4 * i] = v.x; rj[4 * i + 1] = v.y; rj[4 * i + 2] = v.z; rj[4 * i + 3] = v.w;
-      }
-#pragma unroll
-      for (int rt = 0; rt < kTailTiles; ++rt) {
-        if (rt >= tiles) break;
-        f32x16 acc;
-#pragma unroll
-        for (int i = 0; i < 16; ++i) acc[i] = 0.f;
-#pragma unroll
-        for (int kk = 0; kk < 8; ++kk) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[kk], res[rt][kk], acc, 0, 0, 0);
-        float m = acc[0] * rj[0];
-#pragma unroll
-        for (int i = 1; i < 16; i += 3) m = fmaxf(m, fmaxf(acc[i] * rj[i], fmaxf(acc[i + 1] * rj[i + 1], acc[i + 2] * rj[i + 2])));
-        if (__any(m > limit[rt])) {
-          const int own = row[rt] - s * 32 - 4 * half;     // the row itself, in this lane's numbering, if it is here
-          float val = 0.f;
-          int at = -1;
-#pragma unroll
-          for (int i = 0; i < 16; ++i) {
-            const float v = acc[i] * rj[i];
-            const int key = 8 * (i >> 2) + (i & 3);
-            const bool hit = v > limit[rt] && key != own;
-            val = hit ? v : val;
-            at = hit ? key : at;
-          }
-          // keys differ, so the value's bits never decide the maximum
-          if (at >= 0)
-            atomicMax(&best[rt * 32 + lrow], ((unsigned long long)(uint32_t)(s * 32 + 4 * half + at + 1) << 32) | __float_as_uint(val));
-        }
-      }
-    }
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");       // a copy may still be on its way into the buffers
-    __syncthreads();
-    if (wave == 0 && half == 0) {
-#pragma unroll
-      for (int rt = 0; rt < kTailTiles; ++rt)
-        if (g * kTailRows + rt * 32 + lrow < count)
-          sbar[row[rt]] = mean_sim_finish(sbar[row[rt]], r[rt], __uint_as_float((uint32_t)best[rt * 32 + lrow]), a.n);
-    }
-    __syncthreads();
+  for (int rt = 0; rt < TILES; ++rt) {
+    const uint32_t word = words[gram_open_slot(rt * 32 + lrow, rows)];
+    row[rt] = gram_open_row(word);
+    top = max(top, gram_open_below(word));
   }
+#pragma unroll
+  for (int step = 16; step > 0; step >>= 1) top = max(top, __shfl_xor(top, step));
+  const int subtiles = __builtin_amdgcn_readfirstlane(top);
+  // row tile w is copied by wave w into its first buffer, whole rows at a time, and read there by all; the wave's
+  // first subtile of keys goes to the second buffer meanwhile
+  if (wave < tiles) {
+    int of_tile = row[0];                                // row tile `wave`, one row a lane
+#pragma unroll
+    for (int rt = 1; rt < TILES; ++rt) of_tile = wave == rt ? row[rt] : of_tile;
+#pragma unroll
+    for (int jj = 0; jj < 8; ++jj) {
+      const int at = jj * 4 + (lane >> 4);
+      const int from = __shfl(of_tile, at);
+      dma16(kbase, (uint32_t)from * row_bytes + (uint32_t)((lane & 15) ^ (at & 15)) * 16u, lds0 + (uint32_t)(jj * 4 * kRowBytes));
+    }
+  }
+  int s = subtiles - 1 - wave;
+  if (s >= 0) copy_subtile(s, 1);
+#pragma unroll
+  for (int rt = 0; rt < TILES; ++rt) {
+    r[rt] = rn[row[rt]];
+    thr[rt] = rt * 32 + lrow < rows ? a.T / r[rt] : INFINITY;
+  }
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __syncthreads();
+#pragma unroll
+  for (int rt = 0; rt < TILES; ++rt)
+#pragma unroll
+    for (int kk = 0; kk < 8; ++kk)
+      res[rt][kk] = *reinterpret_cast<const bf16x8*>(gram_lds + rt * 2 * kTailSpan + slot_offset(lrow, kk * 2 + half));
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");     // read before the barrier behind which the buffers are used again
+  __syncthreads();
+  for (int buf = 1; s >= 0; s -= NW, buf ^= 1) {
+    // done: a hit above this subtile (the word holds key + 1 in its upper half)
+    float limit[TILES];
+    bool open[TILES], any = false;
+#pragma unroll
+    for (int rt = 0; rt < TILES; ++rt) {
+      const uint32_t met = (uint32_t)(__hip_atomic_load(&best[rt * 32 + lrow], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) >> 32);
+      limit[rt] = met > (uint32_t)(s * 32 + 32) ? INFINITY : thr[rt];
+      open[rt] = __any(limit[rt] != INFINITY);
+      any = any || open[rt];
+    }
+    if (!any) break;
+    copy_subtile(max(s - NW, 0), buf ^ 1);               // the last one is not used
+    asm volatile("s_waitcnt vmcnt(9)" ::: "memory");     // all but the nine copies just issued
+    const unsigned char* tile = mine + buf * kTailSpan;
+    bf16x8 kf[8];
+    float rj[16];
+#pragma unroll
+    for (int kk = 0; kk < 8; ++kk) kf[kk] = *reinterpret_cast<const bf16x8*>(tile + slot_offset(lrow, kk * 2 + half));
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const float4 v = *reinterpret_cast<const float4*>(tile + 32 * kRowBytes + (i * 8 + half * 4) * 4);
+      rj[4 * i] = v.x; rj[4 * i + 1] = v.y; rj[4 * i + 2] = v.z; rj[4 * i + 3] = v.w;
+    }
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // read before this buffer is copied over
+#pragma unroll
+    for (int rt = 0; rt < TILES; ++rt) {
+      if (!open[rt]) continue;
+      f32x16 acc;
+#pragma unroll
+      for (int i = 0; i < 16; ++i) acc[i] = 0.f;
+#pragma unroll
+      for (int kk = 0; kk < 8; ++kk) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[kk], res[rt][kk], acc, 0, 0, 0);
+      float m = acc[0] * rj[0];
+#pragma unroll
+      for (int i = 1; i < 16; i += 3) m = fmaxf(m, fmaxf(acc[i] * rj[i], fmaxf(acc[i + 1] * rj[i + 1], acc[i + 2] * rj[i + 2])));
+      if (__any(m > limit[rt])) {
+        const int own = row[rt] - s * 32 - 4 * half;     // the row itself, in this lane's numbering, if it is here
+        float val = 0.f;
+        int at = -1;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+          const float v = acc[i] * rj[i];
+          const int key = 8 * (i >> 2) + (i & 3);
+          const bool hit = v > limit[rt] && key != own;
+          val = hit ? v : val;
+          at = hit ? key : at;
+        }
+        // keys differ, so the value's bits never decide the maximum
+        if (at >= 0)
+          atomicMax(&best[rt * 32 + lrow], ((unsigned long long)(uint32_t)(s * 32 + 4 * half + at + 1) << 32) | __float_as_uint(val));
+      }
+    }
+  }
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");       // a copy may still be on its way into the buffers
+  __syncthreads();
+  if (wave == 0 && half == 0) {
+#pragma unroll
+    for (int rt = 0; rt < TILES; ++rt)
+      if (rt * 32 + lrow < rows)
+        sbar[row[rt]] = mean_sim_finish(sbar[row[rt]], r[rt], __uint_as_float((uint32_t)best[rt * 32 + lrow]), a.n);
+  }
+  __syncthreads();
+}
+
+// The listed rows of a head, kTailRows at a time.
+template <int NW>
+__global__ __launch_bounds__(NW * 64, 2) void gram_tail_kernel(GramArgs a, int groups) {
+  const int xcd = blockIdx.x & 7;
+  const int q = blockIdx.x >> 3;
+  const int head = (q / groups) * 8 + xcd;               // a head's groups stream the same keys at the same time
+  if (head >= a.heads) return;
+  const int count = *OpenRows::count(a.open, head, a.n_pad);
+  const int p = head / a.H;
+  const uint16_t* kbase = a.k + p * a.ksp + (head - p * a.H) * a.ksh;
+  for (int first = q % groups * kTailRows; first < count; first += groups * kTailRows)
+    tail_group<NW, kTailTiles>(a, head, kbase, OpenRows::words(a.open, head, a.n_pad) + first, min(count - first, kTailRows));
 }
 
 // Workgroups per head: enough for the machine when there are few heads, and one per 128 rows at most (a row block
@@ -947,7 +961,7 @@ __global__ __launch_bounds__(NW * 64, 2) void gram_tail_kernel(GramArgs a, int g
 // unit a head gets eight waves, above that four, and two workgroups share the compute unit.
 template <int NW>
 hipError_t launch_tail_waves(const GramArgs& a, const Plan& pl, hipStream_t stream) {
-  constexpr size_t lds = NW * 2 * kTailSpan;
+  constexpr size_t lds = NW * 2 * kTailSpan + kTailRows * 8;
   static const hipError_t configured = hipFuncSetAttribute(reinterpret_cast<const void*>(&gram_tail_kernel<NW>),
                                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   if (configured != hipSuccess) return configured;

@@ -44,4 +44,11 @@ RKV_HD int gram_copy_lane_row(int lane, int n) {
   return r < n - 1 ? r : n - 1;
 }
 
+// An open row, as it is listed: the row and the subtile of 32 keys below which it is still to be compared.
+RKV_HD unsigned gram_open_word(int row, int below) { return (unsigned)row | ((unsigned)below << 16); }   // row < 2^15, below < 2^10
+RKV_HD int gram_open_row(unsigned word) { return (int)(word & 0xffffu); }
+RKV_HD int gram_open_below(unsigned word) { return (int)(word >> 16); }
+// Place inside a group of `rows` rows that a lane reads for place `at` (past the end: the last one, not used).
+RKV_HD int gram_open_slot(int at, int rows) { return at < rows - 1 ? at : rows - 1; }
+
 }  // namespace rkv

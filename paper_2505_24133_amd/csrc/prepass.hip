@@ -24,7 +24,7 @@ struct PrepassArgs {
   const uint16_t* k;
   float* rnorm;
   unsigned long long* credit;   // zeroed here for the similarity pass, or nullptr
-  unsigned char* open;          // [heads][4 n_pad]: the two words behind a head's list of open rows are zeroed here, or nullptr
+  unsigned char* open;          // [heads][4 n_pad]: the count behind a head's list of open rows is zeroed here, or nullptr
   float* upart;
   float* logit;
   float* stats;
@@ -170,8 +170,7 @@ __global__ __launch_bounds__(kPrepassThreads, 3) void prepass_kernel(PrepassArgs
     for (int m = 0; m < 8; ++m)
       if (j0 + m * 16 + rbase < a.n) *reinterpret_cast<uint4*>(kd + (int64_t)m * 16 * kHeadDim) = regs[m];
   }
-  if (a.open != nullptr && chunk == 0 && t < 2)
-    reinterpret_cast<int*>(a.open + (int64_t)head * a.n_pad * 4 + a.n_pad * 2)[t] = 0;
+  if (a.open != nullptr && chunk == 0 && t == 0) *reinterpret_cast<int*>(a.open + (int64_t)head * a.n_pad * 4 + a.n_pad) = 0;
   if (c16 == 0) {
     // one lane per row writes r (0 in the padding up to n_pad) and clears the partner counter
     float* rn = a.rnorm + (int64_t)head * a.n_pad + j0 + rbase;

@@ -62,3 +62,39 @@ def test_rows_left_open_by_the_scan(P, H, n, clusters, page):
         # 0.02 / n: a partner that is missed changes a mean by at least T / n, a wrong one by 0.1 / n on
         # average; rounding is 2^-22 of a row sum of at most n / clusters + 30, below 0.001
         assert ((mean[p, h].double() - want).abs()[firm] <= 0.02 / n).all()
+
+
+def _segments(P, H, n, segments, clusters, lone, gen):
+    """Keys whose partners lie inside their own one of `segments` stretches, `lone` of them without any; the newest
+    stretch of every other head holds no partners at all, so its row blocks stay in the scan to the end."""
+    part = torch.arange(n, device="cuda") * segments // n
+    cent = torch.randn((P, H, segments * clusters, 128), generator=gen, device="cuda")
+    which = part * clusters + torch.randint(0, clusters, (P, H, n), generator=gen, device="cuda")
+    k = torch.gather(cent, 2, which[..., None].expand(-1, -1, -1, 128))
+    k = k + (0.05 + 0.85 * torch.rand((P, H, n, 1), generator=gen, device="cuda")) * torch.randn(k.shape, generator=gen, device="cuda")
+    alone = torch.rand((P, H, n), generator=gen, device="cuda") < lone
+    alone[:, ::2] |= part == segments - 1
+    return torch.where(alone[..., None], torch.randn(k.shape, generator=gen, device="cuda"), k).bfloat16()
+
+
+@pytest.mark.parametrize("P,H,n,segments,clusters,lone", [
+    pytest.param(40, 8, 1144, 8, 8, 0.2, id="three blocks, leaving one after another"),
+    pytest.param(40, 8, 1144, 1, 8, 0.25, id="a quarter of the rows alone: some blocks leave and some stay"),
+    pytest.param(12, 8, 4300, 8, 12, 0.2, id="twelve blocks, lists of several groups"),
+    pytest.param(70, 8, 2300, 2, 4, 0.22, id="more heads than compute units, several groups for one workgroup"),
+    pytest.param(3, 4, 9000, 3, 40, 0.1, id="few heads, long scans"),
+])
+def test_row_blocks_that_leave_at_different_points(P, H, n, segments, clusters, lone):
+    print(f"[gpu-case] handover mixed P={P} H={H} n={n} segments={segments} lone={lone}", flush=True)
+    T, N = 0.45, n + 8
+    gen = torch.Generator(device="cuda").manual_seed(n + segments)
+    k = _segments(P, H, N, segments, clusters, lone, gen)
+    shape = rkv.Shape(num_problems=P, kv_heads=H, q_heads=H, n_tokens=N, budget=N - 64, sim_threshold=T)
+    _, mean = rkv.rkv_score_redundancy(shape, k, want_mean_sim=True)
+    _, again = rkv.rkv_score_redundancy(shape, k, want_mean_sim=True)
+    assert torch.equal(mean, again)
+    for p, h in {(0, 0), (P // 2, 1), (P - 1, H - 1)}:
+        want, firm = _reference(k[p, h, :n], T)
+        assert firm.float().mean() > 0.5
+        # as above: a row sum is at most n / clusters + 30
+        assert ((mean[p, h].double() - want).abs()[firm] <= 0.02 / n).all()
