@@ -62,7 +62,8 @@ typedef enum {
  * beta entries), so rows in that state take no further part in the pass and the rows still open are
  * gathered into fewer waves as their number falls.  Results are bit-identical to flags = 0; only the
  * amount of matrix work differs (data dependent).  With beta = 1 and T <= 0.9 the default schedule leaves such
- * rows out by itself (unless the pass is split for few heads) and the flag changes nothing.
+ * rows out too, in another way (unless the pass is split for few heads): it is the faster one where nearly all
+ * rows meet a partner among the newest keys, the flag where a third or more of them stay open for long.
  */
 #define RKV_FLAG_SKIP_SATURATED 1u
 /*

@@ -23,8 +23,6 @@
 
 #include "rkv_internal.h"
 
-#include "gram_index.h"
-
 namespace rkv {
 
 namespace {
@@ -1014,7 +1012,6 @@ hipError_t launch_gram(const Plan& pl, const void* k, char* ws, hipStream_t stre
   a.part_pre = reinterpret_cast<float*>(ws + pl.off_ppre);
   a.open = handover(pl) ? reinterpret_cast<unsigned char*>(ws + pl.off_open) : nullptr;
   if (a.open != nullptr) {
-    // (rows that are done are left out here in any case, so RKV_FLAG_SKIP_SATURATED changes nothing)
     const hipError_t e = launch_shape<4, 3, 128, 2, kPlain, false, true, true>(a, pl, stream);
     return e != hipSuccess ? e : launch_tail(a, pl, stream);
   }

@@ -44,6 +44,17 @@ RKV_HD int gram_copy_lane_row(int lane, int n) {
   return r < n - 1 ? r : n - 1;
 }
 
+// Whether a row block leaves the scan with its last open rows: the default direction of the recency rule with beta = 1,
+// one workgroup per row block, T <= 0.9, and no other schedule asked for (`other`: RKV_FLAG_TRIANGULAR_SCAN, the transposed
+// rule, or RKV_FLAG_SKIP_SATURATED, whose gathering of open rows inside a block is the better one where a third or more of
+// the rows stay open: redundancy of 256 heads of n = 4216, 35 % of the rows without a partner, 580 us against 900, of 512
+// heads of n = 2168 370 against 530; where nearly all rows meet one it is the worse, repeated text of n = 1144 80 against 56).
+// Above T = 0.9 only near-copies are partners and too few rows meet one early.  Redundancy, us, full scan / hand-over
+// at T = 0.95: 256 heads of n = 1144 repeated text 91.9 / 92.2, noisy copies 104 / 105, clusters 102 / 103; of
+// n = 4216 936 / 945, 985 / 992, 979 / 1020; 48 heads of noisy copies 250 / 258; 8 heads of n = 32760 repeated text
+// 1713 / 1862.  At T = 0.5 repeated text of n = 1144 takes 57 instead of 92.
+RKV_HD bool gram_handover(float T, int beta, int parts, bool other) { return beta == 1 && parts == 1 && !other && T <= 0.9f; }
+
 // An open row, as it is listed: the row and the subtile of 32 keys below which it is still to be compared.
 RKV_HD unsigned gram_open_word(int row, int below) { return (unsigned)row | ((unsigned)below << 16); }   // row < 2^15, below < 2^10
 RKV_HD int gram_open_row(unsigned word) { return (int)(word & 0xffffu); }

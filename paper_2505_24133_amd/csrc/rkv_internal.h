@@ -5,6 +5,7 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include "gram_index.h"
 #include "rkv.h"
 
 namespace rkv {
@@ -83,12 +84,9 @@ struct Plan {
 };
 
 rkv_status make_plan(const rkv_params* prm, Plan* plan);
-// The similarity pass hands its last open rows to a tail kernel: the default direction of the recency rule with
-// beta = 1, one workgroup per row block, T <= 0.9.  Above that only near-copies are partners, too few rows meet one
-// early for a hand-over (repeated text, T = 0.95, n = 1144: 569 rows open after 8 of 9 tiles) and the empty launch would
-// cost 4.6 us (152.5 -> 157 us for one sequence); at T = 0.5 the same sequence goes from 152 to 120 us.
+// Whether the similarity pass hands its last open rows over (gram_index.h has the rule).
 inline bool handover(const Plan& pl) {
-  return pl.beta == 1 && pl.gram_parts == 1 && !pl.recency_transposed && !pl.triangular && pl.T <= 0.9f;
+  return gram_handover(pl.T, pl.beta, pl.gram_parts, pl.recency_transposed || pl.triangular || pl.skip_saturated);
 }
 int device_compute_units();   // of the current device; cached after the first query
 

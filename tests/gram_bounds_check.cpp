@@ -7,8 +7,19 @@
 
 #include "gram_index.h"
 
+// A schedule that the caller asks for is the one that runs; the hand-over belongs to the default one.
+static bool schedule() {
+  using rkv::gram_handover;
+  if (!gram_handover(0.5f, 1, 1, false) || !gram_handover(0.9f, 1, 1, false)) return std::printf("hand-over left out\n"), false;
+  if (gram_handover(0.5f, 1, 1, true) || gram_handover(0.5f, 2, 1, false) || gram_handover(0.5f, 1, 2, false) ||
+      gram_handover(0.95f, 1, 1, false))
+    return std::printf("hand-over in another schedule\n"), false;
+  return true;
+}
+
 int main(int argc, char** argv) {
   if (argc != 3) return 2;
+  if (!schedule()) return 1;
   const int n = std::atoi(argv[1]), parts = std::atoi(argv[2]);
   const int TC = 128;                               // keys per streamed tile (kGramTile)
   const int nct_all = (n + TC - 1) / TC;

@@ -689,6 +689,8 @@ SKIP_CASES = [
     (_gradual("gradual_split", 2100, 1900, 1, 2, 1, 0.5, 0.9, 0.3, 505), 0),            # beta = 1, few heads: split scan
     (_gradual("gradual_small", 300, 200, 2, 2, 2, 0.5, 0.7, 0.3, 506), 0),              # two row blocks, the second with 36 rows
     (_gradual("none_similar", 1200, 1000, 2, 2, 1, 0.9, 0.0, 0.3, 507), 4),             # nothing is ever met: no row leaves
+    (_gradual("gradual_far", 1500, 1300, 40, 8, 1, 0.95, 0.9, 0.1, 508), 0),            # unsplit, threshold of the full scan
+    (_gradual("gradual_long", 4300, 4100, 12, 8, 1, 0.5, 0.8, 0.3, 509), 0),            # long lists of open rows
 ]
 
 
