@@ -37,7 +37,7 @@ struct GramArgs {
   unsigned long long* credit;   // [heads][n_pad] or nullptr: forgiven similarities charged to the partner
   int* part_cnt;                // [heads][parts][n_pad] hits per row found by one column part
   float* part_pre;              // [heads][parts][n_pad] their sum
-  unsigned char* open;          // [heads][4 n_pad] rows handed to the tail kernel (OpenRows), or nullptr
+  unsigned char* open;          // [heads][4 n_pad] rows handed to the tail kernel (OpenRows)
   int H, heads, n, n_pad, chunks, beta;
   int row_blocks, parts;        // workgroups per head = row_blocks * parts
   int64_t ksp, ksh, kst;
@@ -80,15 +80,20 @@ enum GramVariant : int { kPlain = 0, kSplit = 1, kTransposed = 2, kTriangular = 
 // gathered into the first waves (one row tile each) and the other waves only help copying tiles.
 
 // HANDOVER (the default readings, one workgroup per row block): most rows meet their most recent partner within the
-// first tiles, and streaming all older keys through every workgroup for the last few is what a full scan spends
-// its time on.  Once no more than 1 / kHandoverShare of a block's rows are open, the block appends them to the head's list
-// and ends; gram_tail_kernel takes the listed rows, 128 at a time, against the keys that are left.
-// Measured, us, full scan -> hand-over kernel + tail: 256 heads of n = 1144 82 -> 27 + 16, of n = 4216 869 -> 89 + 96; 6144 heads
-// of n = 2168 5824 -> 899 + 607.  A quarter: a tail row costs about four times a row that stays (its group of 128 streams
-// the keys for itself), and below that the list is short.
+// first tiles, and streaming all older keys past every row for the last few is what a full scan spends its time on.
+// Once no more than 1 / kHandoverShare of a block's rows are open, the block leaves the scan, and its open rows are taken
+// against the keys that are left by tail_group: by the block itself (kOwnTail), or, where many heads have long scans,
+// together with the other blocks' open rows by gram_tail_kernel (kListTail).
+// A quarter: at an eighth blocks with a fifth of their rows alone never leave (redundancy of 256 heads of n = 4216 401 -> 895 us,
+// full scan 890); at a half the tail, whose rows cost more, has too many (8 heads of n = 32760 934 -> 1145).
+// Where no row meets a partner the full scan runs with what the hand-over adds: the looks, and one memory latency for the
+// staged rows.  The rows' closed forms and r_i wait in LDS, so that the scan spills nothing.  Redundancy without partners,
+// us, scan without hand-over / this: 112 heads of n = 1893 115.7 / 116.0, 256 of n = 1144 87.1 / 87.3, 2048 of n = 512
+// 208.6 / 208.1.
 constexpr int kHandoverShare = 4;
-// The list of a head: one word per row (the row, and the subtile of 32 keys below which it is still to be compared), and
-// behind n_pad bytes how many there are.  Which block's rows come first is a matter of chance and changes no result.
+// The list of a head (kListTail): one word per row (the row, and the subtile of 32 keys below which it is still to be
+// compared), and behind n_pad bytes how many there are.  Which block's rows come first is a matter of chance and
+// changes no result.
 // (One restart point for a whole head sent rows that had left late through nearly all keys again: redundancy of 256 heads of
 // n = 4216 whose rows repeat only inside eight segments, a quarter of them nowhere, 1009 us; so 889; full scan 906.)
 struct OpenRows {
@@ -99,17 +104,163 @@ struct OpenRows {
     return reinterpret_cast<int*>(open + (int64_t)head * n_pad * 4 + n_pad);
   }
 };
-constexpr int kHandoverBytes = 64;              // HANDOVER: open-row counts of the waves, the block's place in the list
+
+constexpr int kTailTiles = 4;                            // most row tiles of a group
+constexpr int kTailRows = kTailTiles * 32;
+constexpr int kTailSpan = 32 * kRowBytes + 256;          // one subtile's keys and r_j
+
+// A group of open rows against the older keys, by all NW waves of a workgroup.  Every wave holds the same rows (up to
+// TILES row tiles, MFMA B operand) and takes every NW-th subtile of 32 keys, most recent first, through two LDS buffers of
+// its own: the next subtile's copies are in flight while one is used, no barrier stands in the scan, and the copies are
+// whole rows (fragments read straight from memory touch a quarter of each cache line at a time and ran at a quarter
+// of the rate).  A row is done when a subtile more recent than those a wave still has to look at has met a hit (a
+// maximum of key << 32 | value in LDS); a row tile whose rows are all done is left out.  The products are summed in the
+// same order as in the scan, so a row's result does not depend on who found it.  `words` lists the rows (LDS or memory);
+// their closed forms wait in a.sbar.
+template <int NW, int TILES>
+__device__ __forceinline__ void tail_group(const GramArgs& a, int head, const uint16_t* kbase, const uint32_t* words, int rows) {
+  static_assert(TILES <= NW, "one wave copies each row tile");
+  unsigned long long* best = reinterpret_cast<unsigned long long*>(gram_lds + NW * 2 * kTailSpan);
+  int t = threadIdx.x;
+  asm volatile("" : "+v"(t));                            // (addresses formed from it here are not kept, spilled, from the prologue on)
+  const int lane = t & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int lrow = lane & 31;
+  const int half = lane >> 5;
+  const float* rn = a.rnorm + (int64_t)head * a.n_pad;
+  float* sbar = a.sbar + (int64_t)head * a.n_pad;
+  const uint32_t lds0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(uintptr_t)gram_lds) + wave * 2 * kTailSpan;
+  const unsigned char* mine = gram_lds + wave * 2 * kTailSpan;
+  const uint32_t row_bytes = (uint32_t)a.kst * 2u;
+  // Subtile s covers keys 32 s .. 32 s + 31, all below a tile that the scan has seen and so below n (and the 64 r_j
+  // fetched from 32 s on lie inside the head's n_pad).  Copy jj moves rows 4 jj .. 4 jj + 3 of it.
+  auto copy_subtile = [&](int s, int buf) {
+    const uint64_t src = (uint64_t)(uintptr_t)kbase + (uint64_t)(uint32_t)(s * 32) * row_bytes;
+#pragma unroll
+    for (int jj = 0; jj < 8; ++jj) {
+      const int at = gram_tile_copy_row(jj, lane);
+      dma16(reinterpret_cast<const void*>(src), (uint32_t)at * row_bytes + (uint32_t)((lane & 15) ^ (at & 15)) * 16u,
+            lds0 + (uint32_t)(buf * kTailSpan + jj * 4 * kRowBytes));
+    }
+    dma4(rn + s * 32, (uint32_t)lane * 4u, lds0 + (uint32_t)(buf * kTailSpan + 32 * kRowBytes));
+  };
+  if (t < TILES * 32) best[t] = 0ull;
+  const int tiles = (rows + 31) >> 5;
+  bf16x8 res[TILES][8];
+  float thr[TILES], r[TILES];
+  int row[TILES], top = 0;
+#pragma unroll
+  for (int rt = 0; rt < TILES; ++rt) {
+    const uint32_t word = words[gram_open_slot(rt * 32 + lrow, rows)];
+    row[rt] = gram_open_row(word);
+    top = max(top, gram_open_below(word));
+  }
+#pragma unroll
+  for (int step = 16; step > 0; step >>= 1) top = max(top, __shfl_xor(top, step));
+  const int subtiles = __builtin_amdgcn_readfirstlane(top);
+  // row tile w is copied by wave w into its first buffer, whole rows at a time, and read there by all; the wave's
+  // first subtile of keys goes to the second buffer meanwhile
+  if (wave < tiles) {
+    int of_tile = row[0];                                // row tile `wave`, one row a lane
+#pragma unroll
+    for (int rt = 1; rt < TILES; ++rt) of_tile = wave == rt ? row[rt] : of_tile;
+#pragma unroll
+    for (int jj = 0; jj < 8; ++jj) {
+      const int at = gram_tile_copy_row(jj, lane);
+      const int from = __shfl(of_tile, at);
+      dma16(kbase, (uint32_t)from * row_bytes + (uint32_t)((lane & 15) ^ (at & 15)) * 16u, lds0 + (uint32_t)(jj * 4 * kRowBytes));
+    }
+  }
+  int s = subtiles - 1 - wave;
+  if (s >= 0) copy_subtile(s, 1);
+#pragma unroll
+  for (int rt = 0; rt < TILES; ++rt) {
+    r[rt] = rn[row[rt]];
+    thr[rt] = rt * 32 + lrow < rows ? a.T / r[rt] : INFINITY;
+  }
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __syncthreads();
+#pragma unroll
+  for (int rt = 0; rt < TILES; ++rt)
+#pragma unroll
+    for (int kk = 0; kk < 8; ++kk)
+      res[rt][kk] = *reinterpret_cast<const bf16x8*>(gram_lds + rt * 2 * kTailSpan + slot_offset(lrow, kk * 2 + half));
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");     // read before the barrier behind which the buffers are used again
+  __syncthreads();
+  for (int buf = 1; s >= 0; s -= NW, buf ^= 1) {
+    // done: a hit above this subtile (the word holds key + 1 in its upper half)
+    float limit[TILES];
+    bool open[TILES], any = false;
+#pragma unroll
+    for (int rt = 0; rt < TILES; ++rt) {
+      const uint32_t met = (uint32_t)(__hip_atomic_load(&best[rt * 32 + lrow], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) >> 32);
+      limit[rt] = met > (uint32_t)(s * 32 + 32) ? INFINITY : thr[rt];
+      open[rt] = __any(limit[rt] != INFINITY);
+      any = any || open[rt];
+    }
+    if (!any) break;
+    copy_subtile(max(s - NW, 0), buf ^ 1);               // the last one is not used
+    asm volatile("s_waitcnt vmcnt(9)" ::: "memory");     // all but the nine copies just issued
+    const unsigned char* tile = mine + buf * kTailSpan;
+    bf16x8 kf[8];
+    float rj[16];
+#pragma unroll
+    for (int kk = 0; kk < 8; ++kk) kf[kk] = *reinterpret_cast<const bf16x8*>(tile + slot_offset(lrow, kk * 2 + half));
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const float4 v = *reinterpret_cast<const float4*>(tile + 32 * kRowBytes + (i * 8 + half * 4) * 4);
+      rj[4 * i] = v.x; rj[4 * i + 1] = v.y; rj[4 * i + 2] = v.z; rj[4 * i + 3] = v.w;
+    }
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // read before this buffer is copied over
+#pragma unroll
+    for (int rt = 0; rt < TILES; ++rt) {
+      if (!open[rt]) continue;
+      f32x16 acc;
+#pragma unroll
+      for (int i = 0; i < 16; ++i) acc[i] = 0.f;
+#pragma unroll
+      for (int kk = 0; kk < 8; ++kk) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[kk], res[rt][kk], acc, 0, 0, 0);
+      float m = acc[0] * rj[0];
+#pragma unroll
+      for (int i = 1; i < 16; i += 3) m = fmaxf(m, fmaxf(acc[i] * rj[i], fmaxf(acc[i + 1] * rj[i + 1], acc[i + 2] * rj[i + 2])));
+      if (__any(m > limit[rt])) {
+        const int own = row[rt] - s * 32 - 4 * half;     // the row itself, in this lane's numbering, if it is here
+        float val = 0.f;
+        int at = -1;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+          const float v = acc[i] * rj[i];
+          const int key = 8 * (i >> 2) + (i & 3);
+          const bool hit = v > limit[rt] && key != own;
+          val = hit ? v : val;
+          at = hit ? key : at;
+        }
+        // keys differ, so the value's bits never decide the maximum
+        if (at >= 0)
+          atomicMax(&best[rt * 32 + lrow], ((unsigned long long)(uint32_t)(s * 32 + 4 * half + at + 1) << 32) | __float_as_uint(val));
+      }
+    }
+  }
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");       // a copy may still be on its way into the buffers
+  __syncthreads();
+  if (wave == 0 && half == 0) {
+#pragma unroll
+    for (int rt = 0; rt < TILES; ++rt)
+      if (rt * 32 + lrow < rows)
+        sbar[row[rt]] = mean_sim_finish(sbar[row[rt]], r[rt], __uint_as_float((uint32_t)best[rt * 32 + lrow]), a.n);
+  }
+  __syncthreads();
+}
 
 constexpr int kCompactBytes = 3072;             // SKIP: open-row counts of the waves and the records of moved rows
 
-template <int NW, int RT, int TC, int WPS, int VARIANT, bool SKIP, bool B1, bool HANDOVER>
+template <int NW, int RT, int TC, int WPS, int VARIANT, bool SKIP, bool B1, int HANDOVER>
 __global__ __launch_bounds__(NW * 64, WPS) void gram_kernel(GramArgs a) {
   // WPS = waves per SIMD the register budget is cut for.  With two row tiles per wave there is room for two
   // sets of key fragments and r_j (the next subtile's are fetched a step ahead); with three row tiles (or
   // three waves per SIMD) one set is kept and refilled fragment by fragment behind the subtile's last chain.
   constexpr int KB = (WPS >= 3 || RT >= 3) ? 1 : 2;
-  static_assert(!HANDOVER || (VARIANT == kPlain && B1 && !SKIP), "");
+  static_assert(HANDOVER == kNoTail || (VARIANT == kPlain && B1 && !SKIP), "");
   constexpr int NT = NW * 64;
   constexpr int BM = NW * RT * 32;
   constexpr int NS = TC / 32;                       // 32-key subtiles per tile
@@ -124,7 +275,9 @@ __global__ __launch_bounds__(NW * 64, WPS) void gram_kernel(GramArgs a) {
   constexpr int OFF_U = OFF_RJ + 2 * TC * 4;         // prologue: partial sums of u, one float per thread
   constexpr int OFF_CNT = OFF_U + NT * 4;            // two sets of NW open-row counts (by iteration parity)
   constexpr int OFF_REC = OFF_CNT + 64;              // NW * 32 records of 5 words
-  constexpr int OFF_BASE = OFF_CNT + 2 * NW * 4;     // HANDOVER: the block's first place in the head's list
+  constexpr int OFF_CLOSED = OFF_CNT + 64;           // HANDOVER: the rows' closed-form sums, their r_i, the open rows (or their place in the list)
+  constexpr int OFF_RI = OFF_CLOSED + BM * 4;
+  constexpr int OFF_OPEN = OFF_RI + BM * 4;
   static_assert(64 + NW * 32 * 20 <= kCompactBytes && 2 * NW * 4 <= 64, "record area");
 
   // Workgroups are dealt round-robin to the 8 XCDs; give every XCD whole heads so that a head's
@@ -229,13 +382,13 @@ __global__ __launch_bounds__(NW * 64, WPS) void gram_kernel(GramArgs a) {
   // Rows past n read row n - 1 (their results are never written and their threshold is +inf).
   // (Where the scan is known to be long the fragments are still read directly: their address cycles overlap with the
   // other workgroup's scan, and the copies' second memory latency does not pay: 1 us of 155 for one sequence at T = 0.95.)
-  constexpr bool STAGED_ROWS = HANDOVER || VARIANT == kSplit;
+  constexpr bool STAGED_ROWS = HANDOVER != kNoTail || VARIANT == kSplit;
   static_assert(NW * 32 <= TC && RT <= 3, "a row tile of every wave fits a tile buffer");
   auto copy_row_tile = [&](int rt, int buf) {
 #pragma unroll
     for (int jj = 0; jj < 8; ++jj) {
-      const int at = jj * 4 + (lane >> 4);
-      dma16(kbase, (uint32_t)min(tile_row0(rt) + at, n - 1) * row_bytes + (uint32_t)((lane & 15) ^ (at & 15)) * 16u,
+      const int at = gram_tile_copy_row(jj, lane);
+      dma16(kbase, (uint32_t)gram_own_row(tile_row0(rt), at, n) * row_bytes + (uint32_t)((lane & 15) ^ (at & 15)) * 16u,
             lds0 + (uint32_t)(OFF_TILE + buf * TILE_SPAN + jj * 4 * kRowBytes) + (uint32_t)(wave_s * 32 * kRowBytes));
     }
   };
@@ -260,7 +413,7 @@ __global__ __launch_bounds__(NW * 64, WPS) void gram_kernel(GramArgs a) {
   }
 #pragma unroll
   for (int rt = 0; rt < RT; ++rt) {
-    const int rowc = min(tile_row0(rt) + lrow, n - 1);
+    const int rowc = gram_own_row(tile_row0(rt), lrow, n);
     rni[rt] = rn[rowc];
     if constexpr (!STAGED_ROWS) {
 #pragma unroll
@@ -327,11 +480,15 @@ __global__ __launch_bounds__(NW * 64, WPS) void gram_kernel(GramArgs a) {
       *reinterpret_cast<uint16_t*>(gram_lds + slot_offset(piece, t >> 3) + (t & 7) * 2) = hb;
     }
   }
-  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-  if constexpr (STAGED_ROWS && RT == 3) {
-    read_row_tile(2, 1);
-    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-  }
+  // (staged rows: the third row tile and the first key tile are awaited further down, behind the first two products)
+  auto second_copies = [&]() {
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    if constexpr (STAGED_ROWS && RT == 3) {
+      read_row_tile(2, 1);
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    }
+  };
+  if constexpr (!STAGED_ROWS) second_copies();
   __syncthreads();
 
   // 16-byte A-operand fragments of subtile s: key row lane%32, k-slice (kk, lane/32)
@@ -373,14 +530,36 @@ __global__ __launch_bounds__(NW * 64, WPS) void gram_kernel(GramArgs a) {
     return acc;
   };
   // K_i . u = sum of the three pseudo-key columns (accumulator elements 0..2 of lanes with half == 0)
+  auto row_sum = [&](const bf16x8 (&pf)[8], int rt) {
+    const f32x16 acc = chain(pf, res[rt]);
+    rowdot[rt] = (acc[2] + acc[1]) + acc[0];
+    asm volatile("" : "+v"(rowdot[rt]));         // settle the sum now; the accumulator is dead after this
+  };
+  if constexpr (STAGED_ROWS) {
+    if (active && closing) {
+      bf16x8 pf[8];
+      read_k(pf, gram_lds, 0);
+      row_sum(pf, 0);
+      row_sum(pf, 1);
+    }
+    second_copies();
+    __syncthreads();
+  }
   if (active && closing) {
     bf16x8 pf[8];
     read_k(pf, gram_lds, 0);
 #pragma unroll
-    for (int rt = 0; rt < RT; ++rt) {
-      const f32x16 acc = chain(pf, res[rt]);
-      rowdot[rt] = (acc[2] + acc[1]) + acc[0];
-      asm volatile("" : "+v"(rowdot[rt]));       // settle the sum now; the accumulator is dead after this
+    for (int rt = STAGED_ROWS ? 2 : 0; rt < RT; ++rt) row_sum(pf, rt);
+    if constexpr (HANDOVER != kNoTail) {
+      // kept in LDS: six registers fewer through the scan
+      if (half == 0) {
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt) {
+          const int at = (wave * RT + rt) * 32 + lrow;
+          reinterpret_cast<float*>(gram_lds + OFF_CLOSED)[at] = mean_sim_closed(rni[rt], rowdot[rt], a.eps);
+          reinterpret_cast<float*>(gram_lds + OFF_RI)[at] = rni[rt];
+        }
+      }
     }
   }
 
@@ -560,6 +739,7 @@ __global__ __launch_bounds__(NW * 64, WPS) void gram_kernel(GramArgs a) {
   // part (RT, or 1 in a narrow row block and after open rows have been gathered).  Returns the iteration
   // to go on with in the one-row-tile form, or nct when the scan is over.
   int stop_ct = -1, stop_total = 0, stop_before = 0;   // HANDOVER: last tile scanned, open rows of the block and of the waves before this one
+  int next_look = gram_next_look(-1, nct, false);      // HANDOVER: the next iteration that counts the open rows
   int tiles_now = NW * rte;                            // SKIP: row tiles of the workgroup that may hold open rows
   auto scan = [&](auto rte, int it0) __attribute__((always_inline)) -> int {
   constexpr int RTE = decltype(rte)::value;
@@ -651,9 +831,9 @@ __global__ __launch_bounds__(NW * 64, WPS) void gram_kernel(GramArgs a) {
     }
 
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    if constexpr (HANDOVER) {
+    if constexpr (HANDOVER != kNoTail) {
       // Looked at after tiles 1, 2, 4, 8 and then every eighth: counting costs a wave ~100 cycles of the ~9000 of a tile.
-      const bool look = ((it & (it + 1)) == 0 || (it & 7) == 7) && it + 1 < nct;
+      const bool look = it == next_look;
       int* cbuf = reinterpret_cast<int*>(gram_lds + OFF_CNT) + (it & 1) * NW;
       if (look) {
         int mine = 0;
@@ -676,6 +856,8 @@ __global__ __launch_bounds__(NW * 64, WPS) void gram_kernel(GramArgs a) {
           stop_before = before;
           return nct;
         }
+        // (hardly a row done by a tile's worth of keys: partners are rare here, and the looks up to tile 4 would be in vain)
+        next_look = gram_next_look(it, nct, n - ct * TC >= TC / 2 && total * 8 > min(BM, n - rb * BM) * 7);
       }
     } else if constexpr (!SKIP) {
       __syncthreads();
@@ -760,184 +942,46 @@ __global__ __launch_bounds__(NW * 64, WPS) void gram_kernel(GramArgs a) {
   }
 
   // ---- closed-form row sums minus the forgiven similarities
-  if constexpr (HANDOVER) {
-    if (stop_total > 0) {
-      // the rows still open leave for the tail kernel, which goes on below the last tile scanned: a row's closed
-      // form, its index and that tile
-      int* base = reinterpret_cast<int*>(gram_lds + OFF_BASE);
-      if (t == 0) *base = atomicAdd(OpenRows::count(a.open, head, a.n_pad), stop_total);
-      __syncthreads();
-      uint32_t* list = OpenRows::words(a.open, head, a.n_pad);
-      int slot = *base + stop_before;
-#pragma unroll
-      for (int rt = 0; rt < RT; ++rt) {
-        const bool open = half == 0 && thr[rt] != INFINITY;
-        const unsigned long long ob = __ballot(open);
-        if (open) {
-          const int row = row_of(rt);
-          list[slot + __popcll(ob & ((1ull << lane) - 1ull))] = gram_open_word(row, stop_ct * NS);
-          a.sbar[(int64_t)head * a.n_pad + row] = mean_sim_closed(rni[rt], rowdot[rt], a.eps);
-        } else if (half == 0) {
-          emit(rt);
-        }
-        slot += __popcll(ob);
+  if constexpr (HANDOVER != kNoTail) {
+    // (thread coordinates formed anew: kept from the prologue on they would be spilled)
+    int tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));
+    const int ln = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6), row0 = rb * BM + wv * rte * 32;
+    const float* sums = reinterpret_cast<const float*>(gram_lds + OFF_CLOSED) + wv * RT * 32;
+    const float* rs = reinterpret_cast<const float*>(gram_lds + OFF_RI) + wv * RT * 32;
+    float* out = a.sbar + (int64_t)head * a.n_pad;
+    uint32_t* words = reinterpret_cast<uint32_t*>(gram_lds + OFF_OPEN);
+    int slot = stop_before;
+    if constexpr (HANDOVER == kListTail) {
+      if (stop_total > 0) {
+        if (tid == 0) words[0] = (uint32_t)atomicAdd(OpenRows::count(a.open, head, a.n_pad), stop_total);
+        __syncthreads();
+        slot += (int)words[0];
+        words = OpenRows::words(a.open, head, a.n_pad);
       }
-      return;
     }
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt) {
+      const int i = rt * 32 + (ln & 31);
+      const bool mine = ln < 32 && rt < rte && row0 + i < n;
+      const bool open = mine && stop_total > 0 && thr[rt] != INFINITY;
+      const unsigned long long ob = __ballot(open);
+      if (open) words[slot + __popcll(ob & ((1ull << ln) - 1ull))] = gram_open_word(row0 + i, stop_ct * NS);
+      if (mine) out[row0 + i] = open ? sums[i] : mean_sim_finish(sums[i], rs[i], sub[rt], n);
+      slot += __popcll(ob);
+    }
+    if constexpr (HANDOVER == kOwnTail) {
+      if (stop_total > 0) {
+        __syncthreads();
+        tail_group<NW, BM / kHandoverShare / 32>(a, head, kbase, words, stop_total);
+      }
+    }
+    return;
   }
   if (half == 0) {
 #pragma unroll
     for (int rt = 0; rt < RT; ++rt) emit(rt);
   }
-}
-
-constexpr int kTailTiles = 4;                            // most row tiles of a group
-constexpr int kTailRows = kTailTiles * 32;
-constexpr int kTailSpan = 32 * kRowBytes + 256;          // one subtile's keys and r_j
-
-// A group of open rows against the older keys, by all NW waves of a workgroup.  Every wave holds the same rows (up to
-// TILES row tiles, MFMA B operand) and takes every NW-th subtile of 32 keys, most recent first, through two LDS buffers of
-// its own: the next subtile's copies are in flight while one is used, no barrier stands in the scan, and the copies are
-// whole rows (fragments read straight from memory touch a quarter of each cache line at a time and ran at a quarter
-// of the rate).  A row is done when a subtile more recent than those a wave still has to look at has met a hit (a
-// maximum of key << 32 | value in LDS); a row tile whose rows are all done is left out.  The products are summed in the
-// same order as in the scan, so a row's result does not depend on who found it.  `words` lists the rows; their
-// closed forms wait in a.sbar.
-// Measured on 6144 heads of n = 2168 (about 100 rows a head): 607 us, 5.6 TB/s of keys; 64 rows a group 920, fragments from
-// memory 1785.  Bound: the keys, once per 128 rows; eight waves (64 KB of copies in flight) on a compute unit.
-template <int NW, int TILES>
-__device__ __forceinline__ void tail_group(const GramArgs& a, int head, const uint16_t* kbase, const uint32_t* words, int rows) {
-  static_assert(TILES <= NW, "one wave copies each row tile");
-  unsigned long long* best = reinterpret_cast<unsigned long long*>(gram_lds + NW * 2 * kTailSpan);
-  int t = threadIdx.x;
-  asm volatile("" : "+v"(t));                            // (addresses formed from it here are not kept, spilled, from the prologue on)
-  const int lane = t & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
-  const int lrow = lane & 31;
-  const int half = lane >> 5;
-  const float* rn = a.rnorm + (int64_t)head * a.n_pad;
-  float* sbar = a.sbar + (int64_t)head * a.n_pad;
-  const uint32_t lds0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(uintptr_t)gram_lds) + wave * 2 * kTailSpan;
-  const unsigned char* mine = gram_lds + wave * 2 * kTailSpan;
-  const uint32_t row_bytes = (uint32_t)a.kst * 2u;
-  // Subtile s covers keys 32 s .. 32 s + 31, all below a tile that the scan has seen and so below n (and the 64 r_j
-  // fetched from 32 s on lie inside the head's n_pad).  Copy jj moves rows 4 jj .. 4 jj + 3 of it.
-  auto copy_subtile = [&](int s, int buf) {
-    const uint64_t src = (uint64_t)(uintptr_t)kbase + (uint64_t)(uint32_t)(s * 32) * row_bytes;
-#pragma unroll
-    for (int jj = 0; jj < 8; ++jj) {
-      const int at = jj * 4 + (lane >> 4);
-      dma16(reinterpret_cast<const void*>(src), (uint32_t)at * row_bytes + (uint32_t)((lane & 15) ^ (at & 15)) * 16u,
-            lds0 + (uint32_t)(buf * kTailSpan + jj * 4 * kRowBytes));
-    }
-    dma4(rn + s * 32, (uint32_t)lane * 4u, lds0 + (uint32_t)(buf * kTailSpan + 32 * kRowBytes));
-  };
-  if (t < TILES * 32) best[t] = 0ull;
-  const int tiles = (rows + 31) >> 5;
-  bf16x8 res[TILES][8];
-  float thr[TILES], r[TILES];
-  int row[TILES], top = 0;
-#pragma unroll
-  for (int rt = 0; rt < TILES; ++rt) {
-    const uint32_t word = words[gram_open_slot(rt * 32 + lrow, rows)];
-    row[rt] = gram_open_row(word);
-    top = max(top, gram_open_below(word));
-  }
-#pragma unroll
-  for (int step = 16; step > 0; step >>= 1) top = max(top, __shfl_xor(top, step));
-  const int subtiles = __builtin_amdgcn_readfirstlane(top);
-  // row tile w is copied by wave w into its first buffer, whole rows at a time, and read there by all; the wave's
-  // first subtile of keys goes to the second buffer meanwhile
-  if (wave < tiles) {
-    int of_tile = row[0];                                // row tile `wave`, one row a lane
-#pragma unroll
-    for (int rt = 1; rt < TILES; ++rt) of_tile = wave == rt ? row[rt] : of_tile;
-#pragma unroll
-    for (int jj = 0; jj < 8; ++jj) {
-      const int at = jj * 4 + (lane >> 4);
-      const int from = __shfl(of_tile, at);
-      dma16(kbase, (uint32_t)from * row_bytes + (uint32_t)((lane & 15) ^ (at & 15)) * 16u, lds0 + (uint32_t)(jj * 4 * kRowBytes));
-    }
-  }
-  int s = subtiles - 1 - wave;
-  if (s >= 0) copy_subtile(s, 1);
-#pragma unroll
-  for (int rt = 0; rt < TILES; ++rt) {
-    r[rt] = rn[row[rt]];
-    thr[rt] = rt * 32 + lrow < rows ? a.T / r[rt] : INFINITY;
-  }
-  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-  __syncthreads();
-#pragma unroll
-  for (int rt = 0; rt < TILES; ++rt)
-#pragma unroll
-    for (int kk = 0; kk < 8; ++kk)
-      res[rt][kk] = *reinterpret_cast<const bf16x8*>(gram_lds + rt * 2 * kTailSpan + slot_offset(lrow, kk * 2 + half));
-  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");     // read before the barrier behind which the buffers are used again
-  __syncthreads();
-  for (int buf = 1; s >= 0; s -= NW, buf ^= 1) {
-    // done: a hit above this subtile (the word holds key + 1 in its upper half)
-    float limit[TILES];
-    bool open[TILES], any = false;
-#pragma unroll
-    for (int rt = 0; rt < TILES; ++rt) {
-      const uint32_t met = (uint32_t)(__hip_atomic_load(&best[rt * 32 + lrow], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) >> 32);
-      limit[rt] = met > (uint32_t)(s * 32 + 32) ? INFINITY : thr[rt];
-      open[rt] = __any(limit[rt] != INFINITY);
-      any = any || open[rt];
-    }
-    if (!any) break;
-    copy_subtile(max(s - NW, 0), buf ^ 1);               // the last one is not used
-    asm volatile("s_waitcnt vmcnt(9)" ::: "memory");     // all but the nine copies just issued
-    const unsigned char* tile = mine + buf * kTailSpan;
-    bf16x8 kf[8];
-    float rj[16];
-#pragma unroll
-    for (int kk = 0; kk < 8; ++kk) kf[kk] = *reinterpret_cast<const bf16x8*>(tile + slot_offset(lrow, kk * 2 + half));
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const float4 v = *reinterpret_cast<const float4*>(tile + 32 * kRowBytes + (i * 8 + half * 4) * 4);
-      rj[4 * i] = v.x; rj[4 * i + 1] = v.y; rj[4 * i + 2] = v.z; rj[4 * i + 3] = v.w;
-    }
-    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // read before this buffer is copied over
-#pragma unroll
-    for (int rt = 0; rt < TILES; ++rt) {
-      if (!open[rt]) continue;
-      f32x16 acc;
-#pragma unroll
-      for (int i = 0; i < 16; ++i) acc[i] = 0.f;
-#pragma unroll
-      for (int kk = 0; kk < 8; ++kk) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[kk], res[rt][kk], acc, 0, 0, 0);
-      float m = acc[0] * rj[0];
-#pragma unroll
-      for (int i = 1; i < 16; i += 3) m = fmaxf(m, fmaxf(acc[i] * rj[i], fmaxf(acc[i + 1] * rj[i + 1], acc[i + 2] * rj[i + 2])));
-      if (__any(m > limit[rt])) {
-        const int own = row[rt] - s * 32 - 4 * half;     // the row itself, in this lane's numbering, if it is here
-        float val = 0.f;
-        int at = -1;
-#pragma unroll
-        for (int i = 0; i < 16; ++i) {
-          const float v = acc[i] * rj[i];
-          const int key = 8 * (i >> 2) + (i & 3);
-          const bool hit = v > limit[rt] && key != own;
-          val = hit ? v : val;
-          at = hit ? key : at;
-        }
-        // keys differ, so the value's bits never decide the maximum
-        if (at >= 0)
-          atomicMax(&best[rt * 32 + lrow], ((unsigned long long)(uint32_t)(s * 32 + 4 * half + at + 1) << 32) | __float_as_uint(val));
-      }
-    }
-  }
-  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");       // a copy may still be on its way into the buffers
-  __syncthreads();
-  if (wave == 0 && half == 0) {
-#pragma unroll
-    for (int rt = 0; rt < TILES; ++rt)
-      if (rt * 32 + lrow < rows)
-        sbar[row[rt]] = mean_sim_finish(sbar[row[rt]], r[rt], __uint_as_float((uint32_t)best[rt * 32 + lrow]), a.n);
-  }
-  __syncthreads();
 }
 
 // The listed rows of a head, kTailRows at a time.
@@ -972,11 +1016,12 @@ hipError_t launch_tail(const GramArgs& a, const Plan& pl, hipStream_t stream) {
   return pl.heads <= device_compute_units() ? launch_tail_waves<8>(a, pl, stream) : launch_tail_waves<4>(a, pl, stream);
 }
 
-template <int NW, int RT, int TC, int WPS, int VARIANT, bool SKIP, bool B1 = false, bool HANDOVER = false>
+template <int NW, int RT, int TC, int WPS, int VARIANT, bool SKIP, bool B1 = false, int HANDOVER = kNoTail>
 hipError_t launch_shape(GramArgs a, const Plan& pl, hipStream_t stream) {
   constexpr int BM = NW * RT * 32;
   constexpr size_t lds = kPseudoBytes + 2 * (size_t)TC * kRowBytes + 2 * (size_t)TC * 4 + NW * 64 * 4 +
-                         (SKIP ? kCompactBytes : (HANDOVER ? kHandoverBytes : 0));
+                         (SKIP ? kCompactBytes : (HANDOVER != kNoTail ? 64 + 2 * BM * 4 + BM : 0));
+  static_assert(HANDOVER != kOwnTail || NW * 2 * kTailSpan + BM / kHandoverShare * 8 <= lds - BM, "the tail's buffers lie in front of the open rows");
   // once per kernel instantiation (initialisation of a function-local static is thread-safe)
   static const hipError_t configured =
       hipFuncSetAttribute(reinterpret_cast<const void*>(&gram_kernel<NW, RT, TC, WPS, VARIANT, SKIP, B1, HANDOVER>),
@@ -1010,9 +1055,11 @@ hipError_t launch_gram(const Plan& pl, const void* k, char* ws, hipStream_t stre
   a.row_blocks = 0; a.parts = pl.gram_parts;
   a.part_cnt = reinterpret_cast<int*>(ws + pl.off_pcnt);
   a.part_pre = reinterpret_cast<float*>(ws + pl.off_ppre);
-  a.open = handover(pl) ? reinterpret_cast<unsigned char*>(ws + pl.off_open) : nullptr;
-  if (a.open != nullptr) {
-    const hipError_t e = launch_shape<4, 3, 128, 2, kPlain, false, true, true>(a, pl, stream);
+  a.open = reinterpret_cast<unsigned char*>(ws + pl.off_open);
+  const GramHandover tail = handover(pl);
+  if (tail == kOwnTail) return launch_shape<4, 3, 128, 2, kPlain, false, true, kOwnTail>(a, pl, stream);
+  if (tail == kListTail) {
+    const hipError_t e = launch_shape<4, 3, 128, 2, kPlain, false, true, kListTail>(a, pl, stream);
     return e != hipSuccess ? e : launch_tail(a, pl, stream);
   }
   if (pl.skip_saturated) {

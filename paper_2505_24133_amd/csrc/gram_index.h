@@ -44,6 +44,20 @@ RKV_HD int gram_copy_lane_row(int lane, int n) {
   return r < n - 1 ? r : n - 1;
 }
 
+// A row tile or subtile of 32 rows is moved by eight wave-wide copies; the row inside it that copy jj of a lane moves.
+RKV_HD int gram_tile_copy_row(int jj, int lane) { return jj * 4 + (lane >> 4); }
+// The row a workgroup reads for the row at place `at` of a row tile that begins at row0 (past n: row n - 1).
+RKV_HD int gram_own_row(int row0, int at, int n) { return row0 + at < n - 1 ? row0 + at : n - 1; }
+
+// When a row block may count its open rows (iteration `it` of nct): after tiles 1, 2, 4, 8 and every eighth, as long as
+// what is left of the scan is at least a quarter of what is done.
+RKV_HD bool gram_look(int it, int nct) { return ((it & (it + 1)) == 0 || (it & 7) == 7) && (nct - 1 - it) * 4 >= it + 1; }
+// The iteration of the next such count after `it` (-1: of the first), -1 if there is none; with `rare` none before tile 8.
+RKV_HD int gram_next_look(int it, int nct, bool rare) {
+  const int next = it >= 7 ? it + 8 : (rare ? 7 : it * 2 + 1 + (it < 0));
+  return gram_look(next, nct) ? next : -1;
+}
+
 // Whether a row block leaves the scan with its last open rows: the default direction of the recency rule with beta = 1,
 // one workgroup per row block, T <= 0.9, and no other schedule asked for (`other`: RKV_FLAG_TRIANGULAR_SCAN, the transposed
 // rule, or RKV_FLAG_SKIP_SATURATED, whose gathering of open rows inside a block is the better one where a third or more of
@@ -53,7 +67,19 @@ RKV_HD int gram_copy_lane_row(int lane, int n) {
 // at T = 0.95: 256 heads of n = 1144 repeated text 91.9 / 92.2, noisy copies 104 / 105, clusters 102 / 103; of
 // n = 4216 936 / 945, 985 / 992, 979 / 1020; 48 heads of noisy copies 250 / 258; 8 heads of n = 32760 repeated text
 // 1713 / 1862.  At T = 0.5 repeated text of n = 1144 takes 57 instead of 92.
-RKV_HD bool gram_handover(float T, int beta, int parts, bool other) { return beta == 1 && parts == 1 && !other && T <= 0.9f; }
+// A scan of one tile has nothing to leave.
+// Who takes the rows: the block itself (kOwnTail) reads the older keys once more for the few rows it has left, from L2 where
+// the head's other blocks read them too; the tail kernel (kListTail) reads them once per 128 rows of a head, but is
+// a launch of its own, empty where partners are rare (2 to 3 us).  The line is drawn at what all blocks would read, 500 MB.
+// Redundancy, us, own / list, repeated text: 256 heads of n = 1144 (225 MB) 53.2 / 54.0, of n = 1692 (554 MB) 94 / 104, of
+// n = 2168 (853 MB) 103.2 / 102.4, of n = 4216 (3 GB) 257 / 208; 64 heads of n = 2168 (213 MB) 35.6 / 41.9, 128 (426 MB)
+// 62.7 / 60.9; 48 heads of n = 4216 (584 MB) 76 / 66; 8 heads of n = 32760 (6 GB) 362 / 246.  No partners: 128 heads of
+// n = 2168 137.5 / 139.2, full scan 138.2.
+enum GramHandover : int { kNoTail = 0, kOwnTail = 1, kListTail = 2 };
+RKV_HD GramHandover gram_handover(int heads, int row_blocks, int n, float T, int beta, int parts, bool other) {
+  if (beta != 1 || parts != 1 || other || !(T <= 0.9f) || n <= 128) return kNoTail;
+  return (long long)heads * row_blocks * n * 256 <= 500000000ll ? kOwnTail : kListTail;
+}
 
 // An open row, as it is listed: the row and the subtile of 32 keys below which it is still to be compared.
 RKV_HD unsigned gram_open_word(int row, int below) { return (unsigned)row | ((unsigned)below << 16); }   // row < 2^15, below < 2^10

@@ -84,9 +84,10 @@ struct Plan {
 };
 
 rkv_status make_plan(const rkv_params* prm, Plan* plan);
-// Whether the similarity pass hands its last open rows over (gram_index.h has the rule).
-inline bool handover(const Plan& pl) {
-  return gram_handover(pl.T, pl.beta, pl.gram_parts, pl.recency_transposed || pl.triangular || pl.skip_saturated);
+// Who takes the last open rows of the similarity pass's row blocks (gram_index.h has the rule).
+inline GramHandover handover(const Plan& pl) {
+  return gram_handover(pl.heads, (pl.n + kGramRows - 1) / kGramRows, pl.n, pl.T, pl.beta, pl.gram_parts,
+                       pl.recency_transposed || pl.triangular || pl.skip_saturated);
 }
 int device_compute_units();   // of the current device; cached after the first query
 

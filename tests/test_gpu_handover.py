@@ -98,3 +98,28 @@ def test_row_blocks_that_leave_at_different_points(P, H, n, segments, clusters, 
         assert firm.float().mean() > 0.5
         # as above: a row sum is at most n / clusters + 30
         assert ((mean[p, h].double() - want).abs()[firm] <= 0.02 / n).all()
+
+
+@pytest.mark.parametrize("P,H,n,segments,clusters,lone", [
+    pytest.param(70, 4, 128, 1, 8, 0.1, id="one tile: nothing to leave"),
+    pytest.param(70, 4, 129, 1, 8, 0.1, id="the newest tile holds one key"),
+    pytest.param(70, 4, 256, 1, 6, 0.24, id="two whole tiles"),
+    pytest.param(140, 4, 390, 2, 4, 0.2, id="second block of six rows"),
+    pytest.param(70, 4, 642, 1, 4, 0.2, id="a wave without rows"),
+    pytest.param(70, 4, 642, 1, 400, 0.0, id="hardly a hit: no second look before tile 8"),
+    pytest.param(40, 8, 1144, 1, 200, 0.1, id="leaving late"),
+    pytest.param(40, 8, 1144, 1, 8, 0.25, id="as many rows left as can be"),
+    pytest.param(9, 4, 3457, 4, 8, 0.15, id="few heads, long scan, last tile of one key"),
+    pytest.param(12, 8, 4300, 2, 12, 0.2, id="listed"),
+])
+def test_same_bits_as_the_schedule_without_hand_over(P, H, n, segments, clusters, lone):
+    print(f"[gpu-case] handover bits P={P} H={H} n={n} segments={segments} clusters={clusters} lone={lone}", flush=True)
+    N = n + 8
+    gen = torch.Generator(device="cuda").manual_seed(n + clusters)
+    k = _segments(P, H, N, segments, clusters, lone, gen)
+    mean = {}
+    for flags in (0, rkv.RKV_FLAG_SKIP_SATURATED):
+        shape = rkv.Shape(num_problems=P, kv_heads=H, q_heads=H, n_tokens=N, budget=N - 64, sim_threshold=0.45, flags=flags)
+        mean[flags] = rkv.rkv_score_redundancy(shape, k, want_mean_sim=True)[1]
+    # the flag's kernel keeps every row in its block's scan; both form the same products in the same order
+    assert torch.equal(mean[0], mean[rkv.RKV_FLAG_SKIP_SATURATED])
