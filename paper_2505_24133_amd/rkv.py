@@ -169,8 +169,14 @@ def _ptr(t: Optional[torch.Tensor]) -> Optional[int]:
     return None if t is None else t.data_ptr()
 
 
+# the current stream's handle without a Stream object around it; not a public name, so torch may drop it
+_RAW_STREAM = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream() -> int:
-    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())      # without a Stream object around it
+    if _RAW_STREAM is None:
+        return torch.cuda.current_stream().cuda_stream
+    return _RAW_STREAM(torch.cuda.current_device())
 
 
 def _need_gpu(*tensors: torch.Tensor) -> None:

@@ -26,3 +26,14 @@ def test_packed_block_equals_field_by_field(change):
     q = torch.zeros((2, 8, 4, 128), dtype=torch.bfloat16).transpose(1, 2)
     for args in ({}, dict(k=dense), dict(k=view, v=dense), dict(k=dense, v=view, q=q), dict(q=dense)):
         assert bytes(s.params(**args)) == _by_field(s, **args)
+
+
+def test_stream_handle_without_the_private_call(monkeypatch):
+    class Stream:
+        cuda_stream = 77
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: Stream)
+    monkeypatch.setattr(torch.cuda, "current_device", lambda: 3)
+    monkeypatch.setattr(rkv, "_RAW_STREAM", None)
+    assert rkv._stream() == 77
+    monkeypatch.setattr(rkv, "_RAW_STREAM", lambda device: 100 + device)
+    assert rkv._stream() == 103
