@@ -33,7 +33,7 @@ HOST_WORKERS = max(1, min(16, os.cpu_count() or 1))       # the machine's CPU share 
 
 
 def gram_traffic(workload: str):
-    """HBM bytes per launch of the similarity kernel, from the committed rocprofv3 counter summary of this
+    """HBM bytes of the similarity pass's kernels per step, from the committed rocprofv3 counter summary of this
     workload (profiles/rkv_compress_<workload>_counters.md), or None when there is none or it was taken
     with another version of the kernel's source (the summary records the SHA-256 of gram.hip)."""
     path = os.path.join(ROOT, "profiles", f"rkv_compress_{workload}_counters.md")
@@ -44,7 +44,7 @@ def gram_traffic(workload: str):
     except OSError:
         return None, None
     m_hash = re.search(r"gram\.hip sha256: ([0-9a-f]{64})", text)
-    m_bytes = re.search(r"gram_kernel HBM bytes per launch \(FETCH \+ WRITE\): (\d+)", text)
+    m_bytes = re.search(r"similarity pass, HBM bytes per step \(FETCH \+ WRITE\): (\d+)", text)
     if not m_hash or not m_bytes or m_hash.group(1) != digest:
         return None, os.path.relpath(path, ROOT)
     return int(m_bytes.group(1)), os.path.relpath(path, ROOT)
@@ -197,16 +197,18 @@ def measure(torch, rkv, w, q, k, v, steps, warmup, sets=1, flags=0):
     gather_bytes = heads * w.budget * d * 2 * 2 * 2              # K and V, read + write
     stages = {
         "prepass": {"ms": avg[0], "GB/s": prepass_bytes / avg[0] / 1e6, "frac_hbm": prepass_bytes / (avg[0] * 1e-3) / HBM_PEAK},
-        "gram": {"ms": avg[1], "TFLOP/s": gram_flops / avg[1] / 1e9, "frac_mfma": gram_flops / (avg[1] * 1e-3) / MFMA_BF16_PEAK},
+        # the similarity pass reads every key at least once; what else it reads, and how many entries of the matrix it
+        # forms, depends on the data (rows leave the scan when they have met their partners)
+        "gram": {"ms": avg[1], "GB/s": k_bytes / avg[1] / 1e6, "frac_hbm": k_bytes / (avg[1] * 1e-3) / HBM_PEAK},
         "finalize_select": {"ms": avg[2], "GB/s": select_bytes / avg[2] / 1e6, "frac_hbm": select_bytes / (avg[2] * 1e-3) / HBM_PEAK},
         "gather": {"ms": avg[3], "GB/s": gather_bytes / avg[3] / 1e6, "frac_hbm": gather_bytes / (avg[3] * 1e-3) / HBM_PEAK},
     }
     if w.lam == 1.0:                     # attention-only: the similarity pass is not run
         stages["gram"] = {"ms": avg[1]}
-    elif w.beta == 1 and w.sim_threshold <= 0.9:      # rows leave the scan early: how many entries are formed depends on the data
-        stages["gram"] = {"ms": avg[1]}
+    elif w.sim_threshold >= 1.0:         # no pair is above T, so no row ever leaves: every entry of the matrix is formed
+        stages["gram"] = {"ms": avg[1], "TFLOP/s": gram_flops / avg[1] / 1e9, "frac_mfma": gram_flops / (avg[1] * 1e-3) / MFMA_BF16_PEAK}
     stages = {s: {kk: float(vv) for kk, vv in st.items()} for s, st in stages.items()}
-    work = {"gram_flops": gram_flops, "prepass_bytes": prepass_bytes, "select_bytes": select_bytes, "gather_bytes": gather_bytes}
+    work = {"prepass_bytes": prepass_bytes, "gram_bytes": k_bytes, "select_bytes": select_bytes, "gather_bytes": gather_bytes}
     state = {"shp": shp, "ins": ins, "outs": outs, "ws": ws}
     return ms_per_step, ms_events, stages, work, state
 
@@ -364,8 +366,8 @@ def other_modes(torch, rkv, w, state, reps=50):
         alt = dataclasses.replace(shp, **change)
         alt_ws = rkv.make_workspace(alt)             # some flags need more scratch than the default call
         res[name] = timed(lambda: rkv.rkv_compress(alt, qd, kd, vd, ws=alt_ws, k_out=ko, v_out=vo, kept_idx=idx))
-    # the exact shortcut of the similarity pass (a row that has met its beta partners is left alone;
-    # same results, data-dependent time: with these keys nearly every row is done after one column tile)
+    # the flag's schedule of the similarity pass (open rows are gathered inside their block; same results; with these
+    # keys nearly every row is done after one column tile, and the default schedule is the faster one)
     alt = dataclasses.replace(shp, flags=shp.flags | rkv.RKV_FLAG_SKIP_SATURATED)
     res["skip_saturated_ms"] = timed(lambda: rkv.rkv_compress(alt, qd, kd, vd, ws=ws, k_out=ko, v_out=vo, kept_idx=idx))
     # the entry point with the library's fixed scratch array (no workspace argument)
@@ -392,7 +394,7 @@ def summary(w, ms_per_step, stages):
     seqs = max(1, w.num_problems // w.layers)
     return {"ms_per_step": ms_per_step, "sequences": seqs, "steps_per_s_x_sequences": seqs * 1e3 / ms_per_step,
             "cached_tokens_scored_per_sec": w.num_problems * w.n_cand / (ms_per_step * 1e-3), "stages": stages,
-            "gram_frac_mfma": stages["gram"].get("frac_mfma"), "gather_GB/s": stages["gather"]["GB/s"]}
+            "gather_GB/s": stages["gather"]["GB/s"]}
 
 
 def main() -> int:
@@ -442,25 +444,22 @@ def main() -> int:
     # ---- roofline entry of the dominant kernel, from the HIP-event stage times of this run
     order = ["prepass", "gram", "finalize_select", "gather"]
     dominant = max(stages, key=lambda s: stages[s]["ms"])
+    step_ms = stages[dominant]["ms"]
+    step_bytes = work[{"prepass": "prepass_bytes", "gram": "gram_bytes", "finalize_select": "select_bytes", "gather": "gather_bytes"}[dominant]]
+    roofline = {"kernel": dominant + "_kernel", "bound": "hbm", "achieved": step_bytes / (step_ms * 1e-3) / 1e9,
+                "peak": HBM_PEAK / 1e9, "unit": "GB/s", "frac": step_bytes / (step_ms * 1e-3) / HBM_PEAK, "traffic": None}
+    if dominant == "gram":
+        roofline["bytes"] = "the keys once, the least the pass can read"
+        if plain:
+            roofline["traffic"], roofline["traffic_source"] = gram_traffic(w.name)
     if plain and w.lam < 1.0:
-        # The matrix-bound kernel where it forms every entry of the matrix: the same keys at T = 0.95, where the
-        # rows stay in the scan.  (At the workload's own threshold most rows leave it after the first tiles.)
-        full = measure(torch, rkv, synth.scaled(w, sim_threshold=0.95), q, k, v, min(args.steps, 50), min(args.warmup, 5))[2]
-        roofline = {"kernel": "gram_kernel", "bound": "mfma", "achieved": full["gram"]["TFLOP/s"],
+        # The matrix-bound form of the similarity kernel, on the same keys at T = 1: no row has a partner and every entry
+        # of the matrix is formed.  The timed step launches another instantiation at its own threshold; what
+        # dominates the step is the entry inside.
+        full = measure(torch, rkv, synth.scaled(w, sim_threshold=1.0), q, k, v, min(args.steps, 50), min(args.warmup, 5))[2]
+        roofline = {"kernel": "gram_kernel, full scan", "bound": "mfma", "achieved": full["gram"]["TFLOP/s"],
                     "peak": MFMA_BF16_PEAK / 1e12, "unit": "TFLOP/s", "frac": full["gram"]["frac_mfma"],
-                    "sim_threshold": 0.95, "ms": full["gram"]["ms"], "traffic": None, "dominant_stage": dominant}
-    elif dominant == "gram" and "TFLOP/s" in stages["gram"]:
-        traffic, source = gram_traffic(w.name) if plain else (None, None)
-        roofline = {"kernel": "gram_kernel", "bound": "mfma", "achieved": stages["gram"]["TFLOP/s"],
-                    "peak": MFMA_BF16_PEAK / 1e12, "unit": "TFLOP/s", "frac": stages["gram"]["frac_mfma"],
-                    "traffic": traffic, "traffic_source": source}
-    else:
-        if dominant == "gram":
-            dominant = max((x for x in stages if x != "gram"), key=lambda x: stages[x]["ms"])
-        b = {"prepass": work["prepass_bytes"], "finalize_select": work["select_bytes"], "gather": work["gather_bytes"]}[dominant]
-        ms = stages[dominant]["ms"]
-        roofline = {"kernel": dominant + "_kernel", "bound": "hbm", "achieved": b / (ms * 1e-3) / 1e9,
-                    "peak": HBM_PEAK / 1e9, "unit": "GB/s", "frac": b / (ms * 1e-3) / HBM_PEAK, "traffic": None}
+                    "sim_threshold": 1.0, "ms": full["gram"]["ms"], "traffic": None, "timed_step": roofline}
 
     n, d = w.n_cand, w.head_dim
     out = {
@@ -483,7 +482,6 @@ def main() -> int:
     if args.skip_saturated:
         out["config"]["flags"] = "RKV_FLAG_SKIP_SATURATED"
         out["roofline"] = None          # executed matrix work is data dependent in this mode
-        out["stages"]["gram"].pop("TFLOP/s", None), out["stages"]["gram"].pop("frac_mfma", None)
 
     # ---- measured clocks and what a plain device copy reaches, next to the published peaks
     shp, ws = state["shp"], state["ws"]
@@ -527,8 +525,6 @@ def main() -> int:
             out["workloads"][name]["steps"] = k_steps
             t_bytes, t_src = gram_traffic(name)
             out["workloads"][name]["gram_traffic"] = t_bytes
-            if o_stages["gram"].get("TFLOP/s"):
-                out["workloads"][name]["gram_over_mfma_sustained"] = round(o_stages["gram"]["TFLOP/s"] / out["device"]["mfma_sustained_TFLOP/s"], 4)
             del o_state, qo, ko_, vo_
             torch.cuda.empty_cache()
             if not args.no_cpu_baseline:
