@@ -153,6 +153,8 @@ rkv_status make_plan(const rkv_params* prm, Plan* pl) {
   pl->off_credit = take(pl->recency_transposed || pl->triangular ? heads * np * 8 : 0);
   const size_t parts = (size_t)parts_reserved;
   const bool reports = parts > 1 || pl->triangular;          // per-row reports merged by the finalize kernel
+  // (a split scan reports similarities only; the words reserved for its counts stay, so that the workspace keeps its size
+  // and with it what the fixed scratch array takes)
   pl->off_pcnt = take(reports ? heads * parts * np * 4 : 0);
   pl->off_ppre = take(reports ? heads * parts * np * 4 : 0);
   pl->off_kdense = take(pl->paged ? heads * np * kHeadDim * 2 : 0);

@@ -35,8 +35,8 @@ struct GramArgs {
   const float* upart;
   float* sbar;
   unsigned long long* credit;   // [heads][n_pad] or nullptr: forgiven similarities charged to the partner
-  int* part_cnt;                // [heads][parts][n_pad] hits per row found by one column part
-  float* part_pre;              // [heads][parts][n_pad] their sum
+  int* part_cnt;                // [heads][n_pad] triangular scan: whether the row met an older partner
+  float* part_pre;              // [heads][parts][n_pad] similarity to the partner one column part found, 0 if none
   unsigned char* open;          // [heads][4 n_pad] rows handed to the tail kernel (OpenRows)
   int H, heads, n, n_pad, chunks, beta;
   int row_blocks, parts;        // workgroups per head = row_blocks * parts
@@ -84,6 +84,9 @@ enum GramVariant : int { kPlain = 0, kSplit = 1, kTransposed = 2, kTriangular = 
 // Once no more than 1 / kHandoverShare of a block's rows are open, the block leaves the scan, and its open rows are taken
 // against the keys that are left by tail_group: by the block itself (kOwnTail), or, where many heads have long scans,
 // together with the other blocks' open rows by gram_tail_kernel (kListTail).
+// Measured, us, full scan -> scan with hand-over (+ tail kernel), repeated text at T = 0.5: 256 heads of n = 1144 76 -> 40, of
+// n = 4216 858 -> 73 + 95; 6144 heads of n = 2168 5796 -> 871 + 602 (4.1 and 5.8 TB/s past the L2s, a copy reaches 5.4);
+// 1024 heads of n = 8312, 64 clusters, 13152 -> 618 + 310.
 // A quarter: at an eighth blocks with a fifth of their rows alone never leave (redundancy of 256 heads of n = 4216 401 -> 895 us,
 // full scan 890); at a half the tail, whose rows cost more, has too many (8 heads of n = 32760 934 -> 1145).
 // Where no row meets a partner the full scan runs with what the hand-over adds: the looks, and one memory latency for the
@@ -117,6 +120,9 @@ constexpr int kTailSpan = 32 * kRowBytes + 256;          // one subtile's keys a
 // maximum of key << 32 | value in LDS); a row tile whose rows are all done is left out.  The products are summed in the
 // same order as in the scan, so a row's result does not depend on who found it.  `words` lists the rows (LDS or memory);
 // their closed forms wait in a.sbar.
+// Bound: the keys.  Listed rows read them once per 128: 6144 heads of n = 2168 (about 100 rows a head) 602 us, 5.8 TB/s past the
+// L2s with eight waves (64 KB of copies in flight) on a compute unit; 64 rows a group 920, fragments from memory 1785.  A
+// second subtile in flight gains nothing.  Rows left to their block read them from L2 once per block.
 template <int NW, int TILES>
 __device__ __forceinline__ void tail_group(const GramArgs& a, int head, const uint16_t* kbase, const uint32_t* words, int rows) {
   static_assert(TILES <= NW, "one wave copies each row tile");
@@ -268,7 +274,8 @@ __global__ __launch_bounds__(NW * 64, WPS) void gram_kernel(GramArgs a) {
   static_assert(NW == 2 || NW == 4, "the DMA split assumes 2 or 4 waves");
   static_assert(RT >= 2, "the r_j prefetch needs at least two row tiles per wave");
   static_assert(LOADS % NW == 0, "tile rows must split evenly over the waves");
-  // LDS map: [pseudo-keys | tile 0 | tile 1 | r_j of tile 0 | r_j of tile 1 | u | SKIP: counts, row records]
+  // LDS map: [pseudo-keys | tile 0 | tile 1 | r_j of tile 0 | r_j of tile 1 | u | counts | SKIP: row records, or HANDOVER:
+  // closed forms, r_i, open rows]; the tail lies over everything in front of the counts
   constexpr int OFF_TILE = kPseudoBytes;
   constexpr int TILE_SPAN = LOADS * 1024;            // bytes the DMA copies of one tile cover
   constexpr int OFF_RJ = OFF_TILE + 2 * TILE_SPAN;
@@ -378,7 +385,8 @@ __global__ __launch_bounds__(NW * 64, WPS) void gram_kernel(GramArgs a) {
   // ---- prologue: u -> three bf16 pseudo-keys, the wave's rows -> registers.  The rows travel through the
   // tile buffers, 32 of the wave's in its quarter of each (whole rows a copy: read as fragments straight from
   // memory they cost four times the address cycles, 64 cache lines an instruction: 6144 heads of n = 2168 987 -> 900 us);
-  // the first two row tiles come with the loads for u in one memory latency, the third with the first key tile.
+  // the first two row tiles come with the loads for u in one memory latency, the third with the first key tile in
+  // another, behind the first two row tiles' products with u.
   // Rows past n read row n - 1 (their results are never written and their threshold is +inf).
   // (Where the scan is known to be long the fragments are still read directly: their address cycles overlap with the
   // other workgroup's scan, and the copies' second memory latency does not pay: 1 us of 155 for one sequence at T = 0.95.)
@@ -832,7 +840,8 @@ __global__ __launch_bounds__(NW * 64, WPS) void gram_kernel(GramArgs a) {
 
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     if constexpr (HANDOVER != kNoTail) {
-      // Looked at after tiles 1, 2, 4, 8 and then every eighth: counting costs a wave ~100 cycles of the ~9000 of a tile.
+      // Looked at after tiles 1, 2, 4, 8 and then every eighth (gram_look): a look costs 0.2 us, the wait for the counts
+      // behind the barrier included, of the 4 us of a tile.
       const bool look = it == next_look;
       int* cbuf = reinterpret_cast<int*>(gram_lds + OFF_CNT) + (it & 1) * NW;
       if (look) {

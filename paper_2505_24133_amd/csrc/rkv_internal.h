@@ -71,14 +71,14 @@ struct Plan {
                       //                                 32 keys (groups = 4 * chunks) on the pre-pass's register path
   size_t off_sbar;    // float [heads][n_pad]           mean similarity
   size_t off_imp;     // float [heads][n_pad]           importance (fused path)
-  size_t off_open;    // bytes [heads][4 n_pad]         rows the similarity pass hands to its tail kernel (gram.hip)
+  size_t off_open;    // bytes [heads][4 n_pad]         rows that row blocks list for the tail kernel (gram.hip)
   size_t off_z;       // float [heads][n_pad]           per-head scores Z (shared selection)
   size_t off_credit;  // u64   [heads][n_pad]           forgiven similarity charged to the recent partner, in
                       //                                units of 2^-40 (RKV_FLAG_RECENCY_TRANSPOSED), or the most
                       //                                recent newer partner, row << 32 | similarity bits
                       //                                (RKV_FLAG_TRIANGULAR_SCAN)
-  size_t off_pcnt;    // int   [heads][gram_parts][n_pad]    hits found per row and column part (gram_parts > 1)
-  size_t off_ppre;    // float [heads][gram_parts][n_pad]    sum of those hits
+  size_t off_pcnt;    // int   [heads][n_pad]           triangular scan: whether the row met an older partner
+  size_t off_ppre;    // float [heads][gram_parts][n_pad]    similarity to the partner a column part found (gram_parts > 1)
   size_t off_idx;     // int   [heads][budget]          kept indices when the caller passes none
   size_t total;
 };
