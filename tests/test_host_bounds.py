@@ -1,5 +1,6 @@
-"""Host-side replay of the similarity kernel's key-row copies: for a range of candidate counts and column
-splits no copy names a row outside [0, n), and every copy that is read fetches exactly its tile's rows.
+"""Host-side replay of the similarity kernel's key-row copies and of the hand-over of open rows: for a range of candidate counts
+and column splits no copy names a row outside [0, n), every copy that is read fetches exactly its rows, every row that leaves a
+scan is taken once against all the keys it still has to meet, and the schedule that a caller asks for is the one that runs.
 The row arithmetic is the kernel's own (csrc/gram_index.h, compiled here for the CPU).  CPU only."""
 import os
 import subprocess
