@@ -45,7 +45,8 @@ class DecodeCache:
         """One decode step: k_new, v_new [P, H, d], q_new [P, Hq, d].  Returns True if the step
         ended with a compression."""
         s = self.shape
-        rkv.rkv_cache_append(s, self.k, self.v, self.q_cache, k_new, v_new, q_new,
+        cur = self._cur
+        rkv.rkv_cache_append(s, self._k[cur], self._v[cur], self.q_cache, k_new, v_new, q_new,
                              self.length, self.tokens_seen % s.alpha)
         self.length += 1
         self.tokens_seen += 1

@@ -65,6 +65,7 @@ class RkvError(RuntimeError):
 
 
 _lib = None
+_append = None               # _host.append, once the library is loaded
 
 
 def load_library() -> ctypes.CDLL:
@@ -95,6 +96,13 @@ def load_library() -> ctypes.CDLL:
         getattr(lib, name).restype = ctypes.c_int
     lib.rkv_status_string.argtypes = [ctypes.c_int]
     lib.rkv_status_string.restype = ctypes.c_char_p
+    try:
+        from . import _host
+    except ImportError as e:
+        raise RuntimeError(f"the native host module is missing or does not load ({e}): build it with `python -m paper_2505_24133_amd.build`") from e
+    _host.bind(ctypes.cast(lib.rkv_cache_append, ctypes.c_void_p).value)
+    global _append
+    _append = _host.append
     _lib = lib
     return lib
 
@@ -223,17 +231,16 @@ def rkv_should_compress(shape: Shape, cached_tokens: int) -> bool:
 def rkv_cache_append(shape: Shape, k_cache: torch.Tensor, v_cache: torch.Tensor, q_cache: torch.Tensor,
                      k_new: torch.Tensor, v_new: torch.Tensor, q_new: torch.Tensor, position: int, q_slot: int) -> None:
     """Write one decoded token's key/value rows at `position` and its query state into slot `q_slot`."""
-    P, H, Hq, d = shape.num_problems, shape.kv_heads, shape.q_heads, shape.head_dim
-    kv, bf16 = (P, H, d), torch.bfloat16
-    # called once per decoded token: everything is asked in one expression, and only where it does not hold are
-    # the checks gone through one by one, to say which
-    if not (not shape.page_size and k_cache.shape == (P, H, shape.n_tokens, d) == v_cache.shape
-            and q_cache.shape == (P, Hq, shape.alpha, d) and k_new.shape == kv == v_new.shape and q_new.shape == (P, Hq, d)
-            and k_cache.dtype is v_cache.dtype is q_cache.dtype is k_new.dtype is v_new.dtype is q_new.dtype is bf16
-            and k_cache.stride(3) == 1 and v_cache.stride(3) == 1 and q_cache.stride(3) == 1
-            and k_new.is_contiguous() and v_new.is_contiguous() and q_new.is_contiguous()
-            and k_cache.is_cuda and v_cache.is_cuda and q_cache.is_cuda and k_new.is_cuda and v_new.is_cuda and q_new.is_cuda):
-        _check_append(shape, k_cache, v_cache, q_cache, k_new, v_new, q_new)
+    if _append is None:
+        load_library()
+    # called once per decoded token: a call in order is checked and enqueued in native code; what that does not take (None) is
+    # checked, and answered, here
+    s = _append(shape, k_cache, v_cache, q_cache, k_new, v_new, q_new, position, q_slot)
+    if s is not None:
+        if s != RKV_OK:
+            raise RkvError(s, "rkv_cache_append")
+        return
+    _check_append(shape, k_cache, v_cache, q_cache, k_new, v_new, q_new)
     prm = shape.params(k_cache, v_cache, q=q_cache)
     s = load_library().rkv_cache_append(ctypes.byref(prm), k_cache.data_ptr(), v_cache.data_ptr(), q_cache.data_ptr(),
                                         k_new.data_ptr(), v_new.data_ptr(), q_new.data_ptr(), int(position), int(q_slot), _stream())

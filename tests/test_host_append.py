@@ -1,0 +1,89 @@
+"""The native host path of an appended token: what it takes gives the bytes of the plain call through ctypes, what it does not take is left
+to the binding's own checks, with their errors."""
+import ctypes
+
+import pytest
+import torch
+
+from paper_2505_24133_amd import rkv
+
+
+def _shape(**kw):
+    return rkv.Shape(**{**dict(num_problems=2, kv_heads=2, q_heads=6, n_tokens=40, budget=24), **kw})
+
+
+def _tensors(s, device, strided=False):
+    gen = torch.Generator().manual_seed(5)
+
+    def draw(*size):
+        return torch.randn(size, generator=gen).bfloat16().to(device)
+
+    P, H, Hq, N, a, d = s.num_problems, s.kv_heads, s.q_heads, s.n_tokens, s.alpha, s.head_dim
+    if strided:
+        k, v = draw(P, N + 3, H, d).transpose(1, 2)[:, :, :N], draw(P, H, N + 5, d)[:, :, :N]
+        q = draw(P, a, Hq, d).transpose(1, 2)
+    else:
+        k, v, q = draw(P, H, N, d), draw(P, H, N, d), draw(P, Hq, a, d)
+    return [k, v, q, draw(P, H, d), draw(P, H, d), draw(P, Hq, d)]
+
+
+def test_calls_that_are_not_taken():
+    rkv.load_library()
+    s = _shape()
+    good = _tensors(s, "cpu")
+    assert rkv._append(s, *good, 0, 0) is None                                # not on a GPU
+    assert rkv._append(s, None, *good[1:], 0, 0) is None
+    assert rkv._append(s, *good, 0.0, 0) is None
+    assert rkv._append(s, *good, 1 << 40, 0) is None
+    for wrong in (dict(n_tokens=1 << 40), dict(lam=1), dict(flags=-1), dict(page_size=16)):
+        assert rkv._append(_shape(**wrong), *good, 0, 0) is None
+    assert rkv._append(object(), *good, 0, 0) is None
+    with pytest.raises(TypeError):
+        rkv._append(s, *good)
+    with pytest.raises(RuntimeError, match="GPU tensors only"):
+        rkv.rkv_cache_append(s, *good, 0, 0)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("strided", [False, True])
+def test_same_bytes_as_the_plain_call(strided):
+    print(f"[gpu-case] host append strided={strided}", flush=True)
+    rkv.load_library()
+    s = _shape()
+    native, plain = _tensors(s, "cuda", strided), _tensors(s, "cuda", strided)
+    for row, slot in ((0, 0), (7, 3), (39, 7)):
+        assert rkv._append(s, *native, row, slot) == rkv.RKV_OK
+        prm = s.params(plain[0], plain[1], q=plain[2])
+        assert rkv.load_library().rkv_cache_append(ctypes.byref(prm), *(t.data_ptr() for t in plain), row, slot, rkv._stream()) == rkv.RKV_OK
+        for a, b in zip(native, plain):
+            assert torch.equal(a, b)
+        assert torch.equal(native[0][:, :, row], native[3]) and torch.equal(native[2][:, :, slot], native[5])
+
+
+@pytest.mark.gpu
+def test_stream_and_refusals():
+    print("[gpu-case] host append stream and refusals", flush=True)
+    rkv.load_library()
+    s = _shape()
+    t = _tensors(s, "cuda")
+    other = torch.cuda.Stream()
+    other.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(other):
+        rkv.rkv_cache_append(s, *t, 5, 1)
+    other.synchronize()
+    assert torch.equal(t[1][:, :, 5], t[4])
+    for row, slot in ((40, 0), (-1, 0), (0, 8), (0, -1)):
+        with pytest.raises(rkv.RkvError) as e:
+            rkv.rkv_cache_append(s, *t, row, slot)
+        assert e.value.status == rkv.RKV_ERR_SHAPE
+    for at, bad in ((0, t[0].float()), (3, t[3][:, :1]), (5, t[5].transpose(0, 1).contiguous().transpose(0, 1)), (2, t[2][..., :64]), (1, t[1].cpu())):
+        wrong = list(t)
+        wrong[at] = bad
+        assert rkv._append(s, *wrong, 0, 0) is None
+        with pytest.raises((ValueError, RuntimeError)):
+            rkv.rkv_cache_append(s, *wrong, 0, 0)
+    rkv.rkv_cache_append(s, *t, torch.tensor(6), 2)                           # not an int: the binding's own way
+    assert torch.equal(t[0][:, :, 6], t[3])
+    same = torch.nn.Parameter(t[3], requires_grad=False)                      # nor a plain tensor
+    rkv.rkv_cache_append(s, t[0], t[1], t[2], same, t[4], t[5], 8, 2)
+    assert torch.equal(t[0][:, :, 8], t[3])
