@@ -46,27 +46,6 @@ struct GramArgs {
 
 constexpr int kPseudoBytes = 3 * kRowBytes;     // u as three bf16 pseudo-keys
 
-// 16-byte slot of (row, chunk) inside a tile: rows are 256 bytes, chunks XOR-swizzled by the row, so
-// that 16 consecutive rows read at the same chunk fall into 16 different bank groups.
-__device__ __forceinline__ int slot_offset(int row, int chunk) { return row * kRowBytes + ((chunk ^ (row & 15)) << 4); }
-
-// One wave-wide DMA copy: lane l fetches 16 bytes at base + voff and the hardware stores them
-// at LDS address lds_base + 16 * l.  Issued as inline assembly so that the compiler does not
-// serialise later LDS reads of the *other* buffer behind it; completion is awaited explicitly
-// (vmcnt) before the barrier that publishes the buffer.  M0 is written here and declared clobbered.
-__device__ __forceinline__ void dma16(const void* base, uint32_t voff, uint32_t lds_base) {
-  asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2"
-               :
-               : "s"(lds_base), "v"(voff), "s"(base)
-               : "memory", "m0");
-}
-__device__ __forceinline__ void dma4(const void* base, uint32_t voff, uint32_t lds_base) {
-  asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dword %1, %2"
-               :
-               : "s"(lds_base), "v"(voff), "s"(base)
-               : "memory", "m0");
-}
-
 // Kernel variants (the common one carries none of the others' code):
 //   kPlain       one workgroup scans all columns of its rows and writes the mean similarity
 //   kSplit       the scan is shared by several workgroups, each reports what it found (beta = 1)

@@ -19,7 +19,6 @@ constexpr int kGramTile = 128;       // keys per streamed column tile of the sim
 constexpr int kGramMaxParts = 16;    // most workgroups that share the column scan of one row block
 constexpr int kGramSplitMaxBlocks = 256;   // the scan is split only when all heads have at most this many row blocks
 constexpr int kRowBytes = kHeadDim * 2;
-constexpr int kLdsRowBytes = kRowBytes + 16;   // padded LDS row: 16-byte fragments of 8 consecutive rows hit distinct banks
 
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
 typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16;
@@ -128,6 +127,34 @@ hipError_t launch_append(const Plan& pl, void* k_cache, void* v_cache, void* q_r
                          const void* v_new, const void* q_new, int pos, int slot, hipStream_t stream);
 
 __device__ __forceinline__ float bf16_bits_to_float(uint32_t b) { return __uint_as_float(b << 16); }
+
+// 16-byte slot of (row, chunk) inside a tile: rows are 256 bytes, chunks XOR-swizzled by the row, so
+// that 16 consecutive rows read at the same chunk fall into 16 different bank groups.
+__device__ __forceinline__ int slot_offset(int row, int chunk) { return row * kRowBytes + ((chunk ^ (row & 15)) << 4); }
+
+// One wave-wide DMA copy: lane l fetches 16 bytes at base + voff and the hardware stores them
+// at LDS address lds_base + 16 * l.  Issued as inline assembly so that the compiler does not
+// serialise later LDS reads of the *other* buffer behind it; completion is awaited explicitly
+// (vmcnt) before the barrier that publishes the buffer.  M0 is written here and declared clobbered.
+__device__ __forceinline__ void dma16(const void* base, uint32_t voff, uint32_t lds_base) {
+  asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2"
+               :
+               : "s"(lds_base), "v"(voff), "s"(base)
+               : "memory", "m0");
+}
+__device__ __forceinline__ void dma4(const void* base, uint32_t voff, uint32_t lds_base) {
+  asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dword %1, %2"
+               :
+               : "s"(lds_base), "v"(voff), "s"(base)
+               : "memory", "m0");
+}
+// The same with an address per lane (pages of a paged cache lie further apart than 32 bits reach).
+__device__ __forceinline__ void dma16_far(const void* src, uint32_t lds_base) {
+  asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, off"
+               :
+               : "s"(lds_base), "v"(src)
+               : "memory", "m0");
+}
 
 // Mean similarity of a token (Eq. 6) from its closed-form parts, in ONE fixed sequence of rounded operations
 // wherever it is finished (by the similarity kernel itself, or by the finalize kernel when the token's
