@@ -242,7 +242,7 @@ rkv_status rkv_score_redundancy(const rkv_params* prm, const void* k, float* red
   hipStream_t st = static_cast<hipStream_t>(stream);
   char* w = static_cast<char*>(ws);
   if ((s = hip_status(launch_prepass(pl, nullptr, k, w, st))) != RKV_OK) return s;
-  if ((s = hip_status(launch_gram(pl, k, w, st))) != RKV_OK) return s;
+  if ((s = hip_status(launch_gram(pl, k, w, false, st))) != RKV_OK) return s;
   return hip_status(launch_finalize(pl, kModeRedundancy, w, nullptr, nullptr, nullptr, redundancy, mean_sim,
                                     nullptr, nullptr, st));
 }
@@ -311,10 +311,11 @@ static rkv_status compress_impl(const rkv_params* prm, const void* q_obs, const 
   // lambda == 1 makes Eq. 7 the importance score alone (attention-only eviction): the similarity
   // pass cannot influence the result and is not run.
   const bool attention_only = (pl.lambda == 1.0f);
-  if (!attention_only && (s = hip_status(launch_gram(pl, k, w, st))) != RKV_OK) return s;
+  const bool early = !attention_only && early_importance(pl);
+  if (!attention_only && (s = hip_status(launch_gram(pl, k, w, early, st))) != RKV_OK) return s;
   if ((s = mark(2)) != RKV_OK) return s;
   const int pick = pl.shared_selection ? kModeScore : kModeSelect;
-  const int mode = (attention_only ? kModeImportance : (kModeImportance | kModeRedundancy)) | pick;
+  const int mode = (attention_only ? kModeImportance : (early ? kModeRedundancy : (kModeImportance | kModeRedundancy))) | pick;
   if ((s = hip_status(launch_finalize(pl, mode, w, nullptr, nullptr, nullptr, nullptr, nullptr, score, idx, st))) != RKV_OK)
     return s;
   if (pl.shared_selection && (s = hip_status(launch_shared_select(pl, w, idx, st))) != RKV_OK) return s;

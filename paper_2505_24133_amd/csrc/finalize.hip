@@ -30,7 +30,7 @@ struct FinArgs {
   const float* stats;    // [heads][stat_groups][rows][2]
   float* sbar;           // [heads][n_pad]
   const unsigned long long* credit;   // [heads][n_pad] or nullptr: similarity (units of 2^-40) to take off sbar * n
-  const float* imp_in;   // [heads][n] (select-only mode)
+  const float* imp_in;   // [heads][imp_stride] (modes without the importance stage)
   const float* red_in;   // [heads][n]
   float* imp_out;        // [heads][n] or nullptr
   float* imp_tmp;        // [heads][n_pad] scratch for the fused path
@@ -39,7 +39,7 @@ struct FinArgs {
   float* score_out;      // [heads][n] or nullptr
   float* z_tmp;          // [heads][n_pad] scores for the shared selection, or nullptr
   int32_t* kept;         // [heads][budget]
-  int n, n_pad, stat_groups, alpha, W, k_sel, budget, pool_floats, pool_rows;
+  int n, n_pad, imp_stride, stat_groups, alpha, W, k_sel, budget, pool_floats, pool_rows;
   // similarity rows whose column scan was split over several workgroups: what each part found, merged here
   // (the most recent part that found something) before the softmax
   const float* rnorm;    // [heads][n_pad]
@@ -432,7 +432,7 @@ __global__ __launch_bounds__(kFinThreads, PLAIN == 2 ? 8 : 4) void finalize_kern
     float imp = 0.f, rd = 0.f;
     if constexpr ((MODE & kModeZ) != 0) {
       if constexpr ((MODE & kModeImportance) != 0) imp = imp_dst[i];
-      else imp = a.imp_in[(int64_t)head * n + i];
+      else imp = a.imp_in[(int64_t)head * a.imp_stride + i];
     }
     if constexpr ((MODE & kModeRedundancy) != 0) {
       const float s = sb[i];
@@ -503,6 +503,12 @@ hipError_t launch_finalize(const Plan& pl, int mode, char* ws,
   a.credit = pl.recency_transposed ? reinterpret_cast<const unsigned long long*>(ws + pl.off_credit) : nullptr;
   a.newer = pl.triangular ? reinterpret_cast<const unsigned long long*>(ws + pl.off_credit) : nullptr;
   a.imp_in = imp_in; a.red_in = red_in;
+  a.imp_stride = pl.n;
+  if (mode == (kModeRedundancy | kModeSelect)) {
+    // formed beside the similarity pass
+    a.imp_in = reinterpret_cast<const float*>(ws + pl.off_imp);
+    a.imp_stride = pl.n_pad;
+  }
   a.imp_out = imp_out; a.red_out = red_out; a.sbar_out = sbar_out; a.score_out = score_out;
   a.kept = kept_idx;
   a.n = pl.n; a.n_pad = pl.n_pad; a.stat_groups = pl.chunks * (prepass_register_path(pl) ? 4 : 1); a.alpha = pl.alpha; a.W = pl.W;
@@ -544,6 +550,10 @@ hipError_t launch_finalize(const Plan& pl, int mode, char* ws,
   }
   if (plain_imp && paper_window && default_rule && pl.gram_parts > 1 && mode == (kModeImportance | kModeRedundancy | kModeSelect))
     return launch_plain<kModeImportance | kModeRedundancy | kModeSelect, 3>(a, pl.heads, lds, stream);
+  if (mode == (kModeRedundancy | kModeSelect)) {
+    if (plain_red) return launch_plain<kModeRedundancy | kModeSelect, 2>(a, pl.heads, lds, stream);
+    return launch_plain<kModeRedundancy | kModeSelect, 3>(a, pl.heads, lds, stream);
+  }
   if (plain_imp && paper_window && mode == (kModeImportance | kModeSelect))       // attention-only eviction
     return launch_plain<kModeImportance | kModeSelect, 2>(a, pl.heads, lds, stream);
   if (plain_imp && paper_window && mode == kModeImportance)                       // the stand-alone importance score

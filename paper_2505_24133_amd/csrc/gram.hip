@@ -21,6 +21,7 @@
 #include <algorithm>
 #include <type_traits>
 
+#include "importance.h"
 #include "rkv_internal.h"
 
 namespace rkv {
@@ -42,9 +43,8 @@ struct GramArgs {
   int row_blocks, parts;        // workgroups per head = row_blocks * parts
   int64_t ksp, ksh, kst;
   float T, eps;
+  ImportanceArgs imp;
 };
-
-constexpr int kPseudoBytes = 3 * kRowBytes;     // u as three bf16 pseudo-keys
 
 // Kernel variants (the common one carries none of the others' code):
 //   kPlain       one workgroup scans all columns of its rows and writes the mean similarity
@@ -266,6 +266,12 @@ __global__ __launch_bounds__(NW * 64, WPS) void gram_kernel(GramArgs a) {
   constexpr int OFF_OPEN = OFF_RI + BM * 4;
   static_assert(64 + NW * 32 * 20 <= kCompactBytes && 2 * NW * 4 <= 64, "record area");
 
+  if constexpr (!SKIP && (B1 || VARIANT == kSplit)) {
+    if (a.imp.first != 0 && (int)blockIdx.x >= a.imp.first) {
+      importance_block(a.imp, (int)blockIdx.x - a.imp.first, reinterpret_cast<float*>(gram_lds));
+      return;
+    }
+  }
   // Workgroups are dealt round-robin to the 8 XCDs; give every XCD whole heads so that a head's
   // keys are fetched into one L2 only.  A head's workgroups (row block x column part) are adjacent.
   const int b = blockIdx.x;
@@ -1005,7 +1011,7 @@ hipError_t launch_tail(const GramArgs& a, const Plan& pl, hipStream_t stream) {
 }
 
 template <int NW, int RT, int TC, int WPS, int VARIANT, bool SKIP, bool B1 = false, int HANDOVER = kNoTail>
-hipError_t launch_shape(GramArgs a, const Plan& pl, hipStream_t stream) {
+hipError_t launch_shape(GramArgs a, const Plan& pl, char* ws, bool importance, hipStream_t stream) {
   constexpr int BM = NW * RT * 32;
   constexpr size_t lds = kPseudoBytes + 2 * (size_t)TC * kRowBytes + 2 * (size_t)TC * 4 + NW * 64 * 4 +
                          (SKIP ? kCompactBytes : (HANDOVER != kNoTail ? 64 + 2 * BM * 4 + BM : 0));
@@ -1018,14 +1024,17 @@ hipError_t launch_shape(GramArgs a, const Plan& pl, hipStream_t stream) {
   static_assert(BM == (SKIP ? kGramRowsSkip : kGramRows) && TC == kGramTile, "the plan's split of the similarity pass assumes this shape");
   const int head_groups = (pl.heads + 7) / 8;
   a.row_blocks = (pl.n + BM - 1) / BM;
-  const dim3 grid((unsigned)((int64_t)head_groups * 8 * a.row_blocks * a.parts));
-  hipLaunchKernelGGL((gram_kernel<NW, RT, TC, WPS, VARIANT, SKIP, B1, HANDOVER>), grid, dim3(NW * 64), lds, stream, a);
+  const unsigned blocks = (unsigned)((int64_t)head_groups * 8 * a.row_blocks * a.parts);
+  static_assert(NW * 64 == kImportanceThreads, "one launch");
+  a.imp = importance_args(pl, ws, importance, blocks);
+  hipLaunchKernelGGL((gram_kernel<NW, RT, TC, WPS, VARIANT, SKIP, B1, HANDOVER>), dim3(blocks + importance_blocks(pl, a.imp)), dim3(NW * 64), lds,
+                     stream, a);
   return hipGetLastError();
 }
 
 }  // namespace
 
-hipError_t launch_gram(const Plan& pl, const void* k, char* ws, hipStream_t stream) {
+hipError_t launch_gram(const Plan& pl, const void* k, char* ws, bool importance, hipStream_t stream) {
   GramArgs a;
   a.k = static_cast<const uint16_t*>(k);
   a.rnorm = reinterpret_cast<const float*>(ws + pl.off_rnorm);
@@ -1045,22 +1054,22 @@ hipError_t launch_gram(const Plan& pl, const void* k, char* ws, hipStream_t stre
   a.part_pre = reinterpret_cast<float*>(ws + pl.off_ppre);
   a.open = reinterpret_cast<unsigned char*>(ws + pl.off_open);
   const GramHandover tail = handover(pl);
-  if (tail == kOwnTail) return launch_shape<4, 3, 128, 2, kPlain, false, true, kOwnTail>(a, pl, stream);
+  if (tail == kOwnTail) return launch_shape<4, 3, 128, 2, kPlain, false, true, kOwnTail>(a, pl, ws, importance, stream);
   if (tail == kListTail) {
-    const hipError_t e = launch_shape<4, 3, 128, 2, kPlain, false, true, kListTail>(a, pl, stream);
+    const hipError_t e = launch_shape<4, 3, 128, 2, kPlain, false, true, kListTail>(a, pl, ws, importance, stream);
     return e != hipSuccess ? e : launch_tail(a, pl, stream);
   }
   if (pl.skip_saturated) {
     // (two row tiles per wave: the gathering of open rows needs the registers a third one would take)
-    if (a.credit != nullptr) return launch_shape<4, 2, 128, 2, kTransposed, true>(a, pl, stream);
-    if (a.parts > 1) return launch_shape<4, 2, 128, 2, kSplit, true>(a, pl, stream);
-    return launch_shape<4, 2, 128, 2, kPlain, true>(a, pl, stream);
+    if (a.credit != nullptr) return launch_shape<4, 2, 128, 2, kTransposed, true>(a, pl, ws, importance, stream);
+    if (a.parts > 1) return launch_shape<4, 2, 128, 2, kSplit, true>(a, pl, ws, importance, stream);
+    return launch_shape<4, 2, 128, 2, kPlain, true>(a, pl, ws, importance, stream);
   }
-  if (pl.triangular) return launch_shape<4, 3, 128, 2, kTriangular, false>(a, pl, stream);
-  if (a.credit != nullptr) return launch_shape<4, 3, 128, 2, kTransposed, false>(a, pl, stream);
-  if (a.parts > 1) return launch_shape<4, 3, 128, 2, kSplit, false>(a, pl, stream);       // split only with beta = 1
-  if (pl.beta == 1) return launch_shape<4, 3, 128, 2, kPlain, false, true>(a, pl, stream);
-  return launch_shape<4, 3, 128, 2, kPlain, false>(a, pl, stream);
+  if (pl.triangular) return launch_shape<4, 3, 128, 2, kTriangular, false>(a, pl, ws, importance, stream);
+  if (a.credit != nullptr) return launch_shape<4, 3, 128, 2, kTransposed, false>(a, pl, ws, importance, stream);
+  if (a.parts > 1) return launch_shape<4, 3, 128, 2, kSplit, false>(a, pl, ws, importance, stream);       // split only with beta = 1
+  if (pl.beta == 1) return launch_shape<4, 3, 128, 2, kPlain, false, true>(a, pl, ws, importance, stream);
+  return launch_shape<4, 3, 128, 2, kPlain, false>(a, pl, ws, importance, stream);
 }
 
 }  // namespace rkv

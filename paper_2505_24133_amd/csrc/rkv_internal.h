@@ -19,6 +19,7 @@ constexpr int kGramTile = 128;       // keys per streamed column tile of the sim
 constexpr int kGramMaxParts = 16;    // most workgroups that share the column scan of one row block
 constexpr int kGramSplitMaxBlocks = 256;   // the scan is split only when all heads have at most this many row blocks
 constexpr int kRowBytes = kHeadDim * 2;
+constexpr int kPseudoBytes = 3 * kRowBytes;     // u as three bf16 pseudo-keys
 
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
 typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16;
@@ -96,13 +97,22 @@ int device_compute_units();   // of the current device; cached after the first q
 // per chunk of 128 keys.
 int prepass_register_path(const Plan& pl);
 hipError_t launch_prepass(const Plan& pl, const void* q_obs, const void* k, char* ws, hipStream_t stream);
-hipError_t launch_gram(const Plan& pl, const void* k, char* ws, hipStream_t stream);
+// `importance`: the launch also forms the importance of the candidates (importance.h), as far as early_importance says it can.
+hipError_t launch_gram(const Plan& pl, const void* k, char* ws, bool importance, hipStream_t stream);
+
+// Whether the similarity pass's launch can form the importance too: default readings, the paper's window, the schedules whose
+// kernels carry it, and no more heads than compute units.
+inline bool early_importance(const Plan& pl) {
+  return pl.alpha == 8 && pl.W == 4 && pl.gqa_mode == 0 && !pl.pool_after_mean && !pl.shared_selection && pl.beta == 1 &&
+         !pl.recency_transposed && !pl.triangular && !pl.skip_saturated && pl.heads <= device_compute_units();
+}
 
 enum SelectMode : int {
   kModeImportance = 1,   // workspace logits -> importance
   kModeRedundancy = 2,   // workspace mean similarity -> redundancy
   kModeSelect = 4,       // importance, redundancy -> Z, kept indices (per head)
   kModeScore = 8,        // importance, redundancy -> Z in the workspace, no selection
+                         // (kModeRedundancy | kModeSelect: the importance lies in the workspace already)
 };
 hipError_t launch_finalize(const Plan& pl, int mode, char* ws,
                            const float* imp_in, const float* red_in,
@@ -146,13 +156,6 @@ __device__ __forceinline__ void dma4(const void* base, uint32_t voff, uint32_t l
   asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dword %1, %2"
                :
                : "s"(lds_base), "v"(voff), "s"(base)
-               : "memory", "m0");
-}
-// The same with an address per lane (pages of a paged cache lie further apart than 32 bits reach).
-__device__ __forceinline__ void dma16_far(const void* src, uint32_t lds_base) {
-  asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, off"
-               :
-               : "s"(lds_base), "v"(src)
                : "memory", "m0");
 }
 
