@@ -13,7 +13,7 @@ CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "librkv.so")
 HOST = os.path.join(HERE, "_host" + sysconfig.get_config_var("EXT_SUFFIX"))
-SOURCES = ["api.hip", "prepass.hip", "gram.hip", "finalize.hip", "gather.hip", "compact_inplace.hip", "append.hip", "probe.hip"]
+SOURCES = ["api.hip", "prepass.hip", "gram.hip", "gram_few.hip", "finalize.hip", "gather.hip", "compact_inplace.hip", "append.hip", "probe.hip"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
          "-I", os.path.join(ROOT, "include"), "-I", CSRC]

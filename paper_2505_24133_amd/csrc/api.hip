@@ -131,11 +131,14 @@ rkv_status make_plan(const rkv_params* prm, Plan* pl) {
     const int64_t blocks = (int64_t)pl->heads * ((pl->n + kGramRows - 1) / kGramRows);
     const int nct = (pl->n + kGramTile - 1) / kGramTile;
     pl->gram_parts = 1;
+    pl->few = false;
     if (pl->beta == 1 && !pl->recency_transposed && !pl->triangular && blocks > 0 && blocks <= kGramSplitMaxBlocks) {
       parts_reserved = std::min(nct, kGramMaxParts);
       const int64_t slots = 2 * (int64_t)device_compute_units();
       if (blocks <= slots / 2)
         pl->gram_parts = (int)std::max<int64_t>(1, std::min<int64_t>(parts_reserved, slots / blocks));
+      pl->few = gram_few(pl->heads, pl->n, pl->beta, pl->recency_transposed || pl->triangular || pl->skip_saturated);
+      if (pl->few) pl->gram_parts = nct;
     }
   }
 

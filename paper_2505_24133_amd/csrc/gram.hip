@@ -1035,6 +1035,7 @@ hipError_t launch_shape(GramArgs a, const Plan& pl, char* ws, bool importance, h
 }  // namespace
 
 hipError_t launch_gram(const Plan& pl, const void* k, char* ws, bool importance, hipStream_t stream) {
+  if (pl.few) return launch_gram_few(pl, k, ws, importance, stream);
   GramArgs a;
   a.k = static_cast<const uint16_t*>(k);
   a.rnorm = reinterpret_cast<const float*>(ws + pl.off_rnorm);

@@ -81,6 +81,16 @@ RKV_HD GramHandover gram_handover(int heads, int row_blocks, int n, float T, int
   return (long long)heads * row_blocks * n * 256 <= 500000000ll ? kOwnTail : kListTail;
 }
 
+// Few heads: 128 rows against one column tile a workgroup (gram_few.hip), where a head has at most 16 tiles (so many reports a row
+// the finalize kernel merges at once) and the workgroups, four to a compute unit, make about a round and a half at most.  A whole
+// step, us, blocks of 384 rows / this, T = 0.5 repeated text, T = 0.5 noisy copies, T = 0.95: 2 heads of n = 376 25.1 / 20.2, 26.1 / 20.4,
+// 22.9 / 20.3; 8 of n = 1144 (648 workgroups) 29.2 / 26.7, 29.1 / 26.4, 27.2 / 26.1; 64 of n = 632 (1600) 38.9 / 34.8, 41.0 / 34.4,
+// 36.5 / 34.5; 8 of n = 2032 (2048) 36.5 / 36.0, 39.3 / 36.2, 33.7 / 35.8; 16 of n = 1632 (2704) 39.7 / 39.6, 43.4 / 40.0, 37.1 / 40.1.
+RKV_HD bool gram_few(int heads, int n, int beta, bool other) {
+  const int tiles = (n + 127) / 128;
+  return beta == 1 && !other && tiles > 1 && tiles <= 16 && (long long)heads * tiles * tiles <= 1700;
+}
+
 // An open row, as it is listed: the row and the subtile of 32 keys below which it is still to be compared.
 RKV_HD unsigned gram_open_word(int row, int below) { return (unsigned)row | ((unsigned)below << 16); }   // row < 2^15, below < 2^10
 RKV_HD int gram_open_row(unsigned word) { return (int)(word & 0xffffu); }

@@ -53,6 +53,7 @@ struct Plan {
   // there are too few row blocks to fill the machine (beta = 1 only: each part reports the first hit of
   // its own column range and finalize keeps the most recent one).
   int gram_parts;
+  bool few;                // few heads: one workgroup per 128 rows and column tile (gram_few.hip), gram_parts = column tiles
   int gqa_mode;            // 0: max of the logits, then softmax (Eq. 2-3); 1: softmax, then max; 2: softmax, then mean
   int qrows;               // logit rows kept per head: alpha (mode 0) or G * alpha
   int64_t ksp, ksh, kst;   // key strides (elements)
@@ -99,6 +100,7 @@ int prepass_register_path(const Plan& pl);
 hipError_t launch_prepass(const Plan& pl, const void* q_obs, const void* k, char* ws, hipStream_t stream);
 // `importance`: the launch also forms the importance of the candidates (importance.h), as far as early_importance says it can.
 hipError_t launch_gram(const Plan& pl, const void* k, char* ws, bool importance, hipStream_t stream);
+hipError_t launch_gram_few(const Plan& pl, const void* k, char* ws, bool importance, hipStream_t stream);
 
 // Whether the similarity pass's launch can form the importance too: default readings, the paper's window, the schedules whose
 // kernels carry it, and no more heads than compute units.
