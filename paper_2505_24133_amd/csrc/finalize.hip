@@ -19,6 +19,11 @@ namespace {
 
 constexpr int kFinThreads = 1024;
 constexpr int kFinWaves = kFinThreads / 64;
+// Candidates of a thread whose values are requested at once: a workgroup of its own on a compute unit waits for every one of them, a
+// memory latency each, if they are asked for one by one.  With the runs of the ordered output on odd strides in LDS: 8 heads of n = 32760
+// (32 candidates a thread) 77 -> 54 us, 6144 of n = 2168 232 -> 217, 1024 of n = 8312 133 -> 128;
+// eight cost registers (6144 heads 258).
+constexpr int kBatch = 4;
 // LDS floats of the pooling stage.  With many heads two workgroups share a compute unit (74 KB each);
 // with at most one head per compute unit a workgroup takes up to 128 KB and stages more columns at once.
 constexpr int kMaxPoolFloats = 18944;
@@ -105,20 +110,27 @@ __device__ void select_and_emit(const uint32_t* keys, int n, int k_sel, int alph
   for (int pass = 0; pass < 4; ++pass) {
     const int shift = 24 - 8 * pass;
     uint32_t* h = hist + pass * 256;
-    for (int i0 = 0; i0 < n; i0 += kFinThreads) {
-      const int i = i0 + t;
-      const uint32_t key = (i < n) ? keys[i] : 0u;
-      bool live = (i < n) && ((key & known) == prefix);
-      const uint32_t digit = (key >> shift) & 255u;
-      // scores of one head are often close: count the wave's most common digit with one atomic
-      const unsigned long long am = __ballot(live);
-      if (am != 0ull) {
-        const int first = __builtin_amdgcn_readfirstlane(__ffsll((long long)am) - 1);
-        const uint32_t d0 = (uint32_t)__builtin_amdgcn_readlane((int)digit, first);
-        const unsigned long long same = __ballot(live && digit == d0);
-        if (lane == first) atomicAdd(&h[d0], (uint32_t)__popcll(same));
-        live = live && (digit != d0);
-        if (live) atomicAdd(&h[digit], 1u);
+    for (int base = 0; base < n; base += kBatch * kFinThreads) {
+      uint32_t batch[kBatch];
+#pragma unroll
+      for (int u = 0; u < kBatch; ++u)
+        if (base + u * kFinThreads < n) batch[u] = keys[min(base + u * kFinThreads + t, n - 1)];
+#pragma unroll
+      for (int u = 0; u < kBatch; ++u) {
+        if (base + u * kFinThreads >= n) break;
+        const uint32_t key = batch[u];
+        bool live = base + u * kFinThreads + t < n && ((key & known) == prefix);
+        const uint32_t digit = (key >> shift) & 255u;
+        // scores of one head are often close: count the wave's most common digit with one atomic
+        const unsigned long long am = __ballot(live);
+        if (am != 0ull) {
+          const int first = __builtin_amdgcn_readfirstlane(__ffsll((long long)am) - 1);
+          const uint32_t d0 = (uint32_t)__builtin_amdgcn_readlane((int)digit, first);
+          const unsigned long long same = __ballot(live && digit == d0);
+          if (lane == first) atomicAdd(&h[d0], (uint32_t)__popcll(same));
+          live = live && (digit != d0);
+          if (live) atomicAdd(&h[digit], 1u);
+        }
       }
     }
     __syncthreads();
@@ -144,7 +156,8 @@ __device__ void select_and_emit(const uint32_t* keys, int n, int k_sel, int alph
   // keys > prefix are all kept; of the n_equal keys == prefix the krem with the largest indices.
   // Each thread owns a run of consecutive candidates, so one workgroup scan orders the output.
   const uint32_t skip_eq = n_equal - krem;
-  const int per = (n + kFinThreads - 1) / kFinThreads;
+  // (an odd number of them: the threads of a wave then read from different banks)
+  const int least = (n + kFinThreads - 1) / kFinThreads, per = least > 2 ? least | 1 : least;
   const int lo = min(t * per, n), hi = min(lo + per, n);
   uint32_t gt = 0, eq = 0;
   for (int i = lo; i < hi; ++i) {
@@ -264,7 +277,17 @@ __global__ __launch_bounds__(kFinThreads, PLAIN == 2 ? 8 : 4) void finalize_kern
     // Eq. 6 as it stands: a mean of cosines lies in [-1, 1] (down to -2 with the partner counters taken
     // off), so the exponentials need no shift by the maximum
     float s = 0.f;
-    for (int i = t; i < n; i += kFinThreads) s += __expf(sb[i]);
+    for (int base = 0; base < n; base += kBatch * kFinThreads) {
+      float x[kBatch];
+#pragma unroll
+      for (int u = 0; u < kBatch; ++u)
+        if (base + u * kFinThreads < n) x[u] = sb[min(base + u * kFinThreads + t, n - 1)];
+#pragma unroll
+      for (int u = 0; u < kBatch; ++u) {
+        if (base + u * kFinThreads >= n) break;
+        s = base + u * kFinThreads + t < n ? s + __expf(x[u]) : s;
+      }
+    }
     sinv = 1.0f / block_sum(s, red);
   }
   __syncthreads();
@@ -428,25 +451,38 @@ __global__ __launch_bounds__(kFinThreads, PLAIN == 2 ? 8 : 4) void finalize_kern
   }
 
   // ---- per-candidate redundancy and joint score
-  for (int i = t; i < n; i += kFinThreads) {
-    float imp = 0.f, rd = 0.f;
-    if constexpr ((MODE & kModeZ) != 0) {
-      if constexpr ((MODE & kModeImportance) != 0) imp = imp_dst[i];
-      else imp = a.imp_in[(int64_t)head * a.imp_stride + i];
+  const float* imp_src = nullptr;
+  const float* red_src = nullptr;
+  if constexpr ((MODE & kModeZ) != 0) {
+    imp_src = (MODE & kModeImportance) != 0 ? imp_dst : a.imp_in + (int64_t)head * a.imp_stride;
+    if constexpr ((MODE & kModeRedundancy) == 0) red_src = a.red_in ? a.red_in + (int64_t)head * n : nullptr;   // none: attention-only score
+  }
+  for (int base = 0; base < n; base += kBatch * kFinThreads) {
+    float imp[kBatch], sim[kBatch], red[kBatch];
+#pragma unroll
+    for (int u = 0; u < kBatch; ++u) {
+      if (base + u * kFinThreads >= n) break;
+      const int i = min(base + u * kFinThreads + t, n - 1);
+      imp[u] = (MODE & kModeZ) != 0 ? imp_src[i] : 0.f;
+      sim[u] = (MODE & kModeRedundancy) != 0 ? sb[i] : 0.f;
+      red[u] = red_src != nullptr ? red_src[i] : 0.f;
     }
-    if constexpr ((MODE & kModeRedundancy) != 0) {
-      const float s = sb[i];
-      rd = __expf(s) * sinv;
-      if (a.red_out) a.red_out[(int64_t)head * n + i] = rd;
-      if (a.sbar_out) a.sbar_out[(int64_t)head * n + i] = s;
-    } else if constexpr ((MODE & kModeZ) != 0) {
-      rd = a.red_in ? a.red_in[(int64_t)head * n + i] : 0.f;      // no redundancy input: attention-only score
-    }
-    if constexpr ((MODE & kModeZ) != 0) {
-      const float z = a.lambda * imp - (1.0f - a.lambda) * rd;
-      if (a.score_out) a.score_out[(int64_t)head * n + i] = z;
-      if constexpr ((MODE & kModeScore) != 0) a.z_tmp[(int64_t)head * a.n_pad + i] = z;
-      else keys[i] = order_key(z);
+#pragma unroll
+    for (int u = 0; u < kBatch; ++u) {
+      const int i = base + u * kFinThreads + t;
+      if (i >= n) break;
+      float rd = red[u];
+      if constexpr ((MODE & kModeRedundancy) != 0) {
+        rd = __expf(sim[u]) * sinv;
+        if (a.red_out) a.red_out[(int64_t)head * n + i] = rd;
+        if (a.sbar_out) a.sbar_out[(int64_t)head * n + i] = sim[u];
+      }
+      if constexpr ((MODE & kModeZ) != 0) {
+        const float z = a.lambda * imp[u] - (1.0f - a.lambda) * rd;
+        if (a.score_out) a.score_out[(int64_t)head * n + i] = z;
+        if constexpr ((MODE & kModeScore) != 0) a.z_tmp[(int64_t)head * a.n_pad + i] = z;
+        else keys[i] = order_key(z);
+      }
     }
   }
 
