@@ -246,6 +246,12 @@ __global__ __launch_bounds__(NW * 64, WPS) void gram_kernel(GramArgs a) {
   // three waves per SIMD) one set is kept and refilled fragment by fragment behind the subtile's last chain.
   constexpr int KB = (WPS >= 3 || RT >= 3) ? 1 : 2;
   static_assert(HANDOVER == kNoTail || (VARIANT == kPlain && B1 && !SKIP), "");
+  // HALVES (beta = 1): the keys of a subtile lie in LDS in an order that gives each half of a wave 16 consecutive keys in its
+  // accumulator, the upper half the newer ones: a row's most recent hit is then the last one of a lane, of the upper lane if
+  // it has one, and no key index has to be carried along (gram_index.h): 57 vector instructions instead of 84 where a tile
+  // holds a hit.  Similarity pass, us: 112 heads of n = 1893 with scattered partners 131.0 -> 123.4, 1024 of n = 8312 in 64 clusters
+  // 628 -> 598, 6144 of n = 2168 repeated text 886 -> 861, 256 of n = 1144 at T = 0.95 82.2 -> 80.1.
+  constexpr bool HALVES = B1 && !SKIP;
   constexpr int NT = NW * 64;
   constexpr int BM = NW * RT * 32;
   constexpr int NS = TC / 32;                       // 32-key subtiles per tile
@@ -325,15 +331,15 @@ __global__ __launch_bounds__(NW * 64, WPS) void gram_kernel(GramArgs a) {
   auto issue_rows_clamped = [&](int ct, int buf, int jj) {
     const int row0 = (wave_s + jj * NW) * 4;                   // first of the 4 rows, inside the tile
     const uint32_t dst = lds0 + OFF_TILE + buf * TILE_SPAN + row0 * kRowBytes;
-    const int key = gram_copy_row_clamped(ct, TC, row0, lane, n);
+    const int key = HALVES ? halves_copy_clamped(ct * TC, wave_s, jj, lane, n) : gram_copy_row_clamped(ct, TC, row0, lane, n);
     dma16(kbase, (uint32_t)key * row_bytes + (uint32_t)lane_chunk * 16u, (uint32_t)__builtin_amdgcn_readfirstlane((int)dst));
   };
   // Unclamped form, used inside the scan: per tile one scalar source pointer (the wave's first row of the
   // tile) and one scalar LDS address; the wave's copies lie 16 rows apart in both.
   const uint32_t lane_off = (uint32_t)gram_copy_lane_row(lane, n) * row_bytes + (uint32_t)lane_chunk * 16u;
-  const uint32_t group_step = (uint32_t)gram_copy_group_row(16, TC, n) * row_bytes;
+  const uint32_t group_step = (uint32_t)gram_copy_group_row(HALVES ? halves_copy_row(1) : 16, TC, n) * row_bytes;
   auto tile_source = [&](int ct) -> uint64_t {
-    const int row = gram_copy_tile_row0(ct, TC, n) + gram_copy_group_row(wave_s * 4, TC, n);
+    const int row = gram_copy_tile_row0(ct, TC, n) + gram_copy_group_row(HALVES ? halves_wave_row(wave_s) : wave_s * 4, TC, n);
     const uint64_t addr = (uint64_t)(uintptr_t)kbase + (uint64_t)(uint32_t)row * row_bytes;
     // wave-uniform by construction; readfirstlane returns a signed int, so each half is narrowed to
     // uint32_t before widening (a sign-extended low half would overwrite the high half)
@@ -342,7 +348,8 @@ __global__ __launch_bounds__(NW * 64, WPS) void gram_kernel(GramArgs a) {
     return ((uint64_t)hi << 32) | (uint64_t)lo;
   };
   auto issue_rows = [&](uint64_t src, uint32_t dst, int jj) {
-    dma16(reinterpret_cast<const void*>(src + (uint64_t)((uint32_t)jj * group_step)), lane_off,
+    const uint32_t steps = HALVES ? (uint32_t)(halves_copy_row(jj) / halves_copy_row(1)) : (uint32_t)jj;
+    dma16(reinterpret_cast<const void*>(src + (uint64_t)(steps * group_step)), lane_off,
           dst + (uint32_t)(jj * NW * 4 * kRowBytes));
   };
   auto issue_rj = [&](int ct, int buf) {
@@ -491,11 +498,11 @@ __global__ __launch_bounds__(NW * 64, WPS) void gram_kernel(GramArgs a) {
     for (int kk = 0; kk < 8; ++kk)
       kf[kk] = *reinterpret_cast<const bf16x8*>(tile + slot_offset(row, kk * 2 + half));
   };
-  // r_j of the 16 keys this lane sees in its accumulator: key = 8*(i/4) + 4*half + i%4
+  // r_j of the 16 keys this lane sees in its accumulator: key = 8*(i/4) + 4*half + i%4, or 16*half + i
   auto read_rj = [&](float (&rj)[16], const float* rjs, int s) {
 #pragma unroll
     for (int g = 0; g < 4; ++g) {
-      const float4 v = *reinterpret_cast<const float4*>(rjs + s * 32 + g * 8 + half * 4);
+      const float4 v = *reinterpret_cast<const float4*>(rjs + s * 32 + (HALVES ? half * 16 + g * 4 : g * 8 + half * 4));
       rj[4 * g] = v.x; rj[4 * g + 1] = v.y; rj[4 * g + 2] = v.z; rj[4 * g + 3] = v.w;
     }
   };
@@ -667,36 +674,27 @@ __global__ __launch_bounds__(NW * 64, WPS) void gram_kernel(GramArgs a) {
       cnt[rt] = 1;
     }
   };
-  // beta = 1 (B1): the row's most recent hit in this tile is all that is wanted.  Within a lane the
-  // accumulator elements are in ascending key order, so the last hit met wins; the two lanes of the row
-  // then compare keys.  DIAG: the tile holds the row's own key, which is no partner.
-  auto tile_first_hit = [&](const f32x16& acc, const float (&rj)[16], int rt, int c0, auto diag) {
-    int selfl = row_of(rt) - c0 - 4 * half;                  // own key in this lane's numbering, if it is here
+  // beta = 1 (B1): the row's most recent hit in this tile is all that is wanted.  Within a lane the accumulator elements
+  // are in ascending key order, so the last hit met wins, and the upper half's before the lower half's.  A hit exceeds T >= 0, so 0
+  // says that there is none.  OWN: the tile holds the row's own key, which is no partner.
+  auto tile_first_hit = [&](const f32x16& acc, const float (&rj)[16], int rt, int c0, auto own) __attribute__((always_inline)) {
+    int selfl = row_of(rt) - c0 - 16 * half;                 // own key in this lane's numbering, if it is here
     // keep the 16 comparisons with selfl inside this (rare) path: formed ahead of the scan loop they would
     // occupy 32 scalar registers per row tile for its whole duration
-    if constexpr (decltype(diag)::value) asm volatile("" : "+v"(selfl));
+    if constexpr (decltype(own)::value) asm volatile("" : "+v"(selfl));
     float best = 0.f;
-    int bcol = -1;
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
       const float tvv = acc[i] * rj[i];
-      const int col = 8 * (i >> 2) + (i & 3);
       bool hit = tvv > thr[rt];
-      if constexpr (decltype(diag)::value) hit = hit && (col != selfl);
+      if constexpr (decltype(own)::value) hit = hit && (i != selfl);
       best = hit ? tvv : best;
-      bcol = hit ? col : bcol;
     }
-    const int mycol = bcol < 0 ? -1 : bcol + 4 * half;
-    const auto cols = __builtin_amdgcn_permlane32_swap((unsigned)mycol, (unsigned)mycol, false, false);
     const auto vals = __builtin_amdgcn_permlane32_swap(__float_as_uint(best), __float_as_uint(best), false, false);
-    const bool low = (int)cols[0] > (int)cols[1];
-    const int col = low ? (int)cols[0] : (int)cols[1];
-    const float val = __uint_as_float(low ? vals[0] : vals[1]);
-    if (col >= 0) {
-      sub[rt] += val;
-      cnt[rt] = 1;
-      thr[rt] = INFINITY;
-    }
+    const float older = __uint_as_float(vals[0]), newer = __uint_as_float(vals[1]);
+    const float val = newer != 0.f ? newer : older;
+    sub[rt] += val;
+    thr[rt] = val != 0.f ? INFINITY : thr[rt];
   };
   // Scheduling hint for a block holding one 8-MFMA chain and one tile test (about 24 vector-ALU
   // instructions): issue as 8 x (1 MFMA, 3 VALU) so the test runs in the shadow of the matrix pipe.

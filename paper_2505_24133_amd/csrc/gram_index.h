@@ -44,6 +44,17 @@ RKV_HD int gram_copy_lane_row(int lane, int n) {
   return r < n - 1 ? r : n - 1;
 }
 
+// The scan with beta = 1 keeps a subtile's keys in another order: place q of the 32 holds key halves_key(q), which gives half h
+// of a wave the keys 16 h .. 16 h + 15 of the subtile as its accumulator elements 0 .. 15.  Copy jj of a wave (four rows, at place
+// (wave + 4 jj) * 4 of the tile) then moves rows halves_wave_row(wave) + halves_copy_row(jj) .. + 3 of the tile.
+RKV_HD int halves_key(int q) { return 16 * ((q >> 2) & 1) + 4 * (q >> 3) + (q & 3); }
+RKV_HD int halves_wave_row(int wave) { return 16 * (wave & 1) + 4 * (wave >> 1); }
+RKV_HD int halves_copy_row(int jj) { return 32 * (jj >> 1) + 8 * (jj & 1); }
+RKV_HD int halves_copy_clamped(int tile_row0, int wave, int jj, int lane, int n) {
+  const int r = tile_row0 + halves_wave_row(wave) + halves_copy_row(jj) + (lane >> 4);
+  return r < n - 1 ? r : n - 1;
+}
+
 // A row tile or subtile of 32 rows is moved by eight wave-wide copies; the row inside it that copy jj of a lane moves.
 RKV_HD int gram_tile_copy_row(int jj, int lane) { return jj * 4 + (lane >> 4); }
 // The row a workgroup reads for the row at place `at` of a row tile that begins at row0 (past n: row n - 1).
