@@ -1,8 +1,12 @@
 // Compaction (Alg. 1, gather + concatenate): out[head][r][:] = in[head][kept[head][r]][:] for K and V
-// in one launch.  A row is 256 bytes = 16 lanes x 16 bytes; each thread moves four rows of K and
-// of V with all loads issued before the stores.  Pure HBM traffic; the stores are non-temporal (the
+// in one launch.  A row is 256 bytes = 16 lanes x 16 bytes; each thread moves one such piece of K and of V, and what is
+// in flight on a compute unit are its 32 waves.  Pure HBM traffic; the stores are non-temporal (the
 // compacted rows are not read again by this step, and keeping them out of the caches is worth 15 % of
-// the kernel's time; the same hint on the loads gains nothing and evicts the keys the next step reads).
+// the kernel's time).
+// One row a thread instead of four whose indices (and pages) were asked for one after the other, us: 256 heads, budget 1024
+// 39.1 -> 38.8, 4096 180 -> 177, paged 2048 121 -> 92, 2 heads of 256 4.6 -> 2.8; two or four rows with all indices
+// first lie between.  With non-temporal loads where the caches are too small (gather_streams): 4096 177 -> 151, paged 92 -> 83, 6144
+// heads of 2048 2313 -> 2166 (5.9 TB/s read and written), 1024 of 8192 1503 -> 1435.
 #include "rkv_internal.h"
 
 namespace rkv {
@@ -12,8 +16,7 @@ namespace {
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));   // a type the non-temporal builtins accept
 
 constexpr int kGatherThreads = 256;
-constexpr int kRowsPerThread = 4;
-constexpr int kRowsPerBlock = (kGatherThreads / 16) * kRowsPerThread;   // 64
+constexpr int kRowsPerBlock = kGatherThreads / 16;
 
 struct GatherArgs {
   const uint16_t* k;
@@ -26,39 +29,38 @@ struct GatherArgs {
   int64_t osp, osh, ost;
 };
 
+template <bool PAGED, bool STREAM>
 __global__ __launch_bounds__(kGatherThreads) void gather_kernel(GatherArgs a) {
   const int head = blockIdx.x / a.blocks_per_head;
   const int blk = blockIdx.x - head * a.blocks_per_head;
   const int p = head / a.H;
   const int h = head - p * a.H;
   const int c16 = threadIdx.x & 15;
-  const int slot = threadIdx.x >> 4;
-  const uint16_t* kb = a.k + c16 * 8;
-  const uint16_t* vb = a.v + c16 * 8;
-  const int32_t* kept = a.kept + (int64_t)head * a.budget;
-  u32x4 kr[kRowsPerThread], vr[kRowsPerThread];
-  int rows[kRowsPerThread];
-#pragma unroll
-  for (int m = 0; m < kRowsPerThread; ++m) {
-    rows[m] = blk * kRowsPerBlock + m * (kGatherThreads / 16) + slot;
-    kr[m] = u32x4{0, 0, 0, 0};
-    vr[m] = u32x4{0, 0, 0, 0};
-    if (rows[m] < a.budget) {
-      int src = kept[rows[m]];
-      src = min(max(src, 0), a.N - 1);
-      kr[m] = *reinterpret_cast<const u32x4*>(kb + a.kl.offset(p, h, src));
-      vr[m] = *reinterpret_cast<const u32x4*>(vb + a.vl.offset(p, h, src));
-    }
+  const int row = blk * kRowsPerBlock + (threadIdx.x >> 4);
+  if (row >= a.budget) return;
+  const int src = min(max(a.kept[(int64_t)head * a.budget + row], 0), a.N - 1);
+  int64_t ko, vo;
+  if constexpr (PAGED) {
+    const int64_t page = a.kl.table[(int64_t)p * a.kl.table_stride + (src >> a.kl.page_shift)];
+    const int64_t in_page = src & ((1 << a.kl.page_shift) - 1);
+    ko = page * a.kl.spage + h * a.kl.sh + in_page * a.kl.st;
+    vo = page * a.vl.spage + h * a.vl.sh + in_page * a.vl.st;
+  } else {
+    ko = p * a.kl.sp + h * a.kl.sh + (int64_t)src * a.kl.st;
+    vo = p * a.vl.sp + h * a.vl.sh + (int64_t)src * a.vl.st;
   }
-#pragma unroll
-  for (int m = 0; m < kRowsPerThread; ++m) {
-    if (rows[m] < a.budget) {
-      const int64_t o = p * a.osp + h * a.osh + (int64_t)rows[m] * a.ost + c16 * 8;
-      __builtin_nontemporal_store(kr[m], reinterpret_cast<u32x4*>(a.k_out + o));
-      __builtin_nontemporal_store(vr[m], reinterpret_cast<u32x4*>(a.v_out + o));
-    }
-  }
+  const u32x4* kp = reinterpret_cast<const u32x4*>(a.k + ko + c16 * 8);
+  const u32x4* vp = reinterpret_cast<const u32x4*>(a.v + vo + c16 * 8);
+  const u32x4 kr = STREAM ? __builtin_nontemporal_load(kp) : *kp;
+  const u32x4 vr = STREAM ? __builtin_nontemporal_load(vp) : *vp;
+  const int64_t o = p * a.osp + h * a.osh + (int64_t)row * a.ost + c16 * 8;
+  __builtin_nontemporal_store(kr, reinterpret_cast<u32x4*>(a.k_out + o));
+  __builtin_nontemporal_store(vr, reinterpret_cast<u32x4*>(a.v_out + o));
 }
+
+// Caches too large for the 256 MB behind the L2s are read past it: the pre-pass's keys are long gone from there and nothing reads
+// these rows again.  Below that the keys are still there (256 heads of n = 1152, 150 MB of K and V: 38.8 us, non-temporal 39.9).
+bool gather_streams(const Plan& pl) { return (int64_t)pl.heads * pl.N * kRowBytes * 2 > (256ll << 20); }
 
 }  // namespace
 
@@ -75,7 +77,9 @@ hipError_t launch_gather(const Plan& pl, const void* k, const void* v, const int
   a.kl = k_layout(pl); a.vl = v_layout(pl);
   a.osp = pl.osp; a.osh = pl.osh; a.ost = pl.ost;
   const dim3 grid((unsigned)((int64_t)pl.heads * a.blocks_per_head));
-  hipLaunchKernelGGL(gather_kernel, grid, dim3(kGatherThreads), 0, stream, a);
+  auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, dim3(kGatherThreads), 0, stream, a); };
+  if (gather_streams(pl)) launch(pl.paged ? gather_kernel<true, true> : gather_kernel<false, true>);
+  else launch(pl.paged ? gather_kernel<true, false> : gather_kernel<false, false>);
   return hipGetLastError();
 }
 
