@@ -6,7 +6,7 @@
 // One row a thread instead of four whose indices (and pages) were asked for one after the other, us: 256 heads, budget 1024
 // 39.1 -> 38.8, 4096 180 -> 177, paged 2048 121 -> 92, 2 heads of 256 4.6 -> 2.8; two or four rows with all indices
 // first lie between.  With non-temporal loads where the caches are too small (gather_streams): 4096 177 -> 151, paged 92 -> 83, 6144
-// heads of 2048 2313 -> 2166 (5.9 TB/s read and written), 1024 of 8192 1503 -> 1435.
+// heads of 2048 2313 -> 2166 to 2310 (where the buffers lie decides; 5.6 to 5.9 TB/s read and written), 1024 of 8192 1503 -> 1420.
 #include "rkv_internal.h"
 
 namespace rkv {
