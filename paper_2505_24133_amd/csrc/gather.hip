@@ -7,6 +7,8 @@
 // 39.1 -> 38.8, 4096 180 -> 177, paged 2048 121 -> 92, 2 heads of 256 4.6 -> 2.8; two or four rows with all indices
 // first lie between.  With non-temporal loads where the caches are too small (gather_streams): 4096 177 -> 151, paged 92 -> 83, 6144
 // heads of 2048 2313 -> 2166 to 2310 (where the buffers lie decides; 5.6 to 5.9 TB/s read and written), 1024 of 8192 1503 -> 1420.
+#include <algorithm>
+
 #include "rkv_internal.h"
 
 namespace rkv {
@@ -17,6 +19,9 @@ typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));   // a type the 
 
 constexpr int kGatherThreads = 256;
 constexpr int kRowsPerBlock = kGatherThreads / 16;
+// A launch takes fewer than 2^32 work items in a dimension.  Calls with more blocks are made in several launches, up to the number of
+// rows that one launch of 64 rows a block takes (2^30, 512 GB of outputs).
+constexpr int64_t kMaxBlocks = (1ll << 32) / kGatherThreads - 1;
 
 struct GatherArgs {
   const uint16_t* k;
@@ -25,14 +30,16 @@ struct GatherArgs {
   uint16_t* k_out;
   uint16_t* v_out;
   int H, N, budget, blocks_per_head;
+  uint32_t first;              // block of the whole call that this launch begins with
   KvLayout kl, vl;
   int64_t osp, osh, ost;
 };
 
 template <bool PAGED, bool STREAM>
 __global__ __launch_bounds__(kGatherThreads) void gather_kernel(GatherArgs a) {
-  const int head = blockIdx.x / a.blocks_per_head;
-  const int blk = blockIdx.x - head * a.blocks_per_head;
+  const uint32_t block = a.first + blockIdx.x;
+  const int head = (int)(block / (uint32_t)a.blocks_per_head);
+  const int blk = (int)block - head * a.blocks_per_head;
   const int p = head / a.H;
   const int h = head - p * a.H;
   const int c16 = threadIdx.x & 15;
@@ -73,14 +80,22 @@ hipError_t launch_gather(const Plan& pl, const void* k, const void* v, const int
   a.k_out = static_cast<uint16_t*>(k_out);
   a.v_out = static_cast<uint16_t*>(v_out);
   a.H = pl.H; a.N = pl.N; a.budget = pl.budget;
-  a.blocks_per_head = (pl.budget + kRowsPerBlock - 1) / kRowsPerBlock;
+  a.blocks_per_head = (int)(((int64_t)pl.budget + kRowsPerBlock - 1) / kRowsPerBlock);
   a.kl = k_layout(pl); a.vl = v_layout(pl);
   a.osp = pl.osp; a.osh = pl.osh; a.ost = pl.ost;
-  const dim3 grid((unsigned)((int64_t)pl.heads * a.blocks_per_head));
-  auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, dim3(kGatherThreads), 0, stream, a); };
-  if (gather_streams(pl)) launch(pl.paged ? gather_kernel<true, true> : gather_kernel<false, true>);
-  else launch(pl.paged ? gather_kernel<true, false> : gather_kernel<false, false>);
-  return hipGetLastError();
+  if (pl.heads * (((int64_t)pl.budget + 63) / 64) > kMaxBlocks) return hipErrorInvalidConfiguration;
+  const int64_t blocks = (int64_t)pl.heads * a.blocks_per_head;
+  auto launch = [&](auto kernel) {
+    hipError_t e = hipSuccess;
+    for (int64_t first = 0; first < blocks && e == hipSuccess; first += kMaxBlocks) {
+      a.first = (uint32_t)first;
+      hipLaunchKernelGGL(kernel, dim3((unsigned)std::min(blocks - first, kMaxBlocks)), dim3(kGatherThreads), 0, stream, a);
+      e = hipGetLastError();
+    }
+    return e;
+  };
+  if (gather_streams(pl)) return launch(pl.paged ? gather_kernel<true, true> : gather_kernel<false, true>);
+  return launch(pl.paged ? gather_kernel<true, false> : gather_kernel<false, false>);
 }
 
 }  // namespace rkv

@@ -1,0 +1,68 @@
+"""The launches of the gather of kept rows: none holds more work items than the runtime takes, and calls that need more than one are whole."""
+import os
+import subprocess
+
+import pytest
+import torch
+
+from paper_2505_24133_amd import build as B
+from paper_2505_24133_amd import rkv
+
+
+@pytest.fixture(scope="module")
+def recorder(repo_root, tmp_path_factory):
+    if not os.path.exists(B.LIB):
+        B.build()
+    exe = str(tmp_path_factory.mktemp("launches") / "launch_record")
+    subprocess.run(["g++", "-O1", "-Wall", "-D__HIP_PLATFORM_AMD__", "-I", os.path.join(repo_root, "include"), "-I", "/opt/rocm/include",
+                    os.path.join(repo_root, "tests", "launch_record.cpp"), "-o", exe, "-rdynamic", B.LIB, "-L/opt/rocm/lib", "-lamdhip64",
+                    f"-Wl,-rpath,{os.path.dirname(B.LIB)}:/opt/rocm/lib"], check=True)
+    return exe
+
+
+@pytest.mark.parametrize("P,H,N,budget,page,launches", [
+    pytest.param(1, 2, 40, 16, 0, 1, id="one block a head"),
+    pytest.param(1, 1, 40, 17, 16, 1, id="a block of one row"),
+    pytest.param(1 << 19, 8, 40, 32, 0, 1, id="a half of what a launch takes"),
+    pytest.param(1 << 19, 8, 80, 64, 0, 2, id="one block more than a launch takes"),
+    pytest.param(420000, 8, 100, 80, 0, 2, id="3.36 million heads of 80 rows"),
+    pytest.param(1 << 19, 8, 80, 64, 16, 2, id="paged"),
+    pytest.param(1, 1, 40, (1 << 28) + 1, 0, 2, id="one long list"),
+    pytest.param(1 << 18, 8, 600, 448, 0, 4, id="four launches"),
+])
+def test_every_launch_is_one_the_runtime_takes(recorder, P, H, N, budget, page, launches):
+    r = subprocess.run([recorder, *map(str, (P, H, N, budget, page))], capture_output=True, text=True)
+    assert r.returncode == 0, r.stdout + r.stderr
+    word = r.stdout.split()
+    assert [int(word[1]), int(word[3]), int(word[5])] == [rkv.RKV_OK, launches, P * H * -(-budget // 16)], r.stdout
+    assert int(word[7]) * 256 < 1 << 32
+
+
+def test_what_was_too_large_stays_refused(recorder):
+    r = subprocess.run([recorder, str(1 << 19), "8", "400", "256", "0"], capture_output=True, text=True)
+    assert r.stdout.startswith(f"status {rkv.RKV_ERR_HIP} launches 0 "), r.stdout
+
+
+@pytest.mark.gpu
+def test_rows_of_a_second_launch():
+    """2^22 heads of 49 rows (four blocks each): 2^24 blocks, one more than a launch takes.  The heads of eight share a page, K and V and the
+    two outputs are one buffer each, so that 53 GB suffice; the outputs are compared in pieces."""
+    P, H, budget, page = 1 << 19, 8, 49, 64
+    rows = P * H * budget
+    if torch.cuda.mem_get_info()[0] < rows * 256 + rows * 4 + (12 << 30):
+        pytest.skip("needs 66 GB of GPU memory")
+    print(f"[gpu-case] gather in two launches P={P} H={H} budget={budget}", flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    pool = torch.randn((8, H, page, 128), generator=gen, device="cuda").bfloat16()
+    table = torch.randint(0, 8, (P, 1), generator=gen, device="cuda").int()
+    shape = rkv.Shape(num_problems=P, kv_heads=H, q_heads=H, n_tokens=page, budget=budget, page_size=page, block_table=table)
+    kept = torch.randint(0, page, (P, H, budget), generator=gen, device="cuda", dtype=torch.int32)
+    out = torch.empty((P, H, budget, 128), dtype=torch.bfloat16, device="cuda")
+    out[0] = 7.0
+    out[-2:] = 7.0
+    rkv.rkv_compact(shape, pool, pool, kept, k_out=out, v_out=out)
+    piece = 1 << 13
+    heads = torch.arange(H, device="cuda")[None, :, None]
+    for p in (0, P // 2, P - piece):
+        part = slice(p, p + piece)
+        assert torch.equal(out[part], pool[table[part].long()[:, :, None], heads, kept[part].long()])
