@@ -19,11 +19,14 @@ namespace {
 
 constexpr int kFinThreads = 1024;
 constexpr int kFinWaves = kFinThreads / 64;
-// Candidates of a thread whose values are requested at once: a workgroup of its own on a compute unit waits for every one of them, a
-// memory latency each, if they are asked for one by one.  With the runs of the ordered output on odd strides in LDS: 8 heads of n = 32760
-// (32 candidates a thread) 77 -> 54 us, 6144 of n = 2168 232 -> 217, 1024 of n = 8312 133 -> 128;
-// eight cost registers (6144 heads 258).
+// How many of a thread's candidates the kernel requests from memory at once (BATCH).  One after the other is a memory latency each where a
+// workgroup has a compute unit to itself, but four at a time is more code to fetch, which is what a call of few candidates waits for.  So
+// four above kBatchFrom candidates (three a thread) in the step's own instantiations, one everywhere else.  One / four, us: a step of
+// 8 heads of n = 1024 22.1 / 22.4, 2048 32.7 / 32.7, 2992 41.9 / 41.7, 4096 58.0 / 57.5, 32760 766 / 759; 1600 heads of n = 100 71.1 / 71.7;
+// 6144 of n = 2168 4665 / 4653.  Eight cost registers.  The stand-alone selection, with its counting loop in batches too: 8 heads of
+// n = 100 4.6 / 5.0, 1600 of 512 16.1 / 18.4, 1600 of 4096 39.6 / 40.7.
 constexpr int kBatch = 4;
+constexpr int kBatchFrom = 2 * kFinThreads;
 // LDS floats of the pooling stage.  With many heads two workgroups share a compute unit (74 KB each);
 // with at most one head per compute unit a workgroup takes up to 128 KB and stages more columns at once.
 constexpr int kMaxPoolFloats = 18944;
@@ -35,7 +38,7 @@ struct FinArgs {
   const float* stats;    // [heads][stat_groups][rows][2]
   float* sbar;           // [heads][n_pad]
   const unsigned long long* credit;   // [heads][n_pad] or nullptr: similarity (units of 2^-40) to take off sbar * n
-  const float* imp_in;   // [heads][imp_stride] (modes without the importance stage)
+  const float* imp_in;   // [heads][n] (select-only mode), [heads][n_pad] (importance formed beside the similarity pass)
   const float* red_in;   // [heads][n]
   float* imp_out;        // [heads][n] or nullptr
   float* imp_tmp;        // [heads][n_pad] scratch for the fused path
@@ -44,7 +47,7 @@ struct FinArgs {
   float* score_out;      // [heads][n] or nullptr
   float* z_tmp;          // [heads][n_pad] scores for the shared selection, or nullptr
   int32_t* kept;         // [heads][budget]
-  int n, n_pad, imp_stride, stat_groups, alpha, W, k_sel, budget, pool_floats, pool_rows;
+  int n, n_pad, stat_groups, alpha, W, k_sel, budget, pool_floats, pool_rows;
   // similarity rows whose column scan was split over several workgroups: what each part found, merged here
   // (the most recent part that found something) before the softmax
   const float* rnorm;    // [heads][n_pad]
@@ -110,27 +113,20 @@ __device__ void select_and_emit(const uint32_t* keys, int n, int k_sel, int alph
   for (int pass = 0; pass < 4; ++pass) {
     const int shift = 24 - 8 * pass;
     uint32_t* h = hist + pass * 256;
-    for (int base = 0; base < n; base += kBatch * kFinThreads) {
-      uint32_t batch[kBatch];
-#pragma unroll
-      for (int u = 0; u < kBatch; ++u)
-        if (base + u * kFinThreads < n) batch[u] = keys[min(base + u * kFinThreads + t, n - 1)];
-#pragma unroll
-      for (int u = 0; u < kBatch; ++u) {
-        if (base + u * kFinThreads >= n) break;
-        const uint32_t key = batch[u];
-        bool live = base + u * kFinThreads + t < n && ((key & known) == prefix);
-        const uint32_t digit = (key >> shift) & 255u;
-        // scores of one head are often close: count the wave's most common digit with one atomic
-        const unsigned long long am = __ballot(live);
-        if (am != 0ull) {
-          const int first = __builtin_amdgcn_readfirstlane(__ffsll((long long)am) - 1);
-          const uint32_t d0 = (uint32_t)__builtin_amdgcn_readlane((int)digit, first);
-          const unsigned long long same = __ballot(live && digit == d0);
-          if (lane == first) atomicAdd(&h[d0], (uint32_t)__popcll(same));
-          live = live && (digit != d0);
-          if (live) atomicAdd(&h[digit], 1u);
-        }
+    for (int i0 = 0; i0 < n; i0 += kFinThreads) {
+      const int i = i0 + t;
+      const uint32_t key = (i < n) ? keys[i] : 0u;
+      bool live = (i < n) && ((key & known) == prefix);
+      const uint32_t digit = (key >> shift) & 255u;
+      // scores of one head are often close: count the wave's most common digit with one atomic
+      const unsigned long long am = __ballot(live);
+      if (am != 0ull) {
+        const int first = __builtin_amdgcn_readfirstlane(__ffsll((long long)am) - 1);
+        const uint32_t d0 = (uint32_t)__builtin_amdgcn_readlane((int)digit, first);
+        const unsigned long long same = __ballot(live && digit == d0);
+        if (lane == first) atomicAdd(&h[d0], (uint32_t)__popcll(same));
+        live = live && (digit != d0);
+        if (live) atomicAdd(&h[digit], 1u);
       }
     }
     __syncthreads();
@@ -156,7 +152,8 @@ __device__ void select_and_emit(const uint32_t* keys, int n, int k_sel, int alph
   // keys > prefix are all kept; of the n_equal keys == prefix the krem with the largest indices.
   // Each thread owns a run of consecutive candidates, so one workgroup scan orders the output.
   const uint32_t skip_eq = n_equal - krem;
-  // (an odd number of them: the threads of a wave then read from different banks)
+  // (an odd number of them: the threads of a wave then read from different banks; the stand-alone selection of 8 heads of n = 32760
+  // 61 -> 49 us)
   const int least = (n + kFinThreads - 1) / kFinThreads, per = least > 2 ? least | 1 : least;
   const int lo = min(t * per, n), hi = min(lo + per, n);
   uint32_t gt = 0, eq = 0;
@@ -189,7 +186,7 @@ constexpr int kModeZ = kModeSelect | kModeScore;     // modes that form the join
 // The instantiations for the default readings with the paper's window sizes keep to 64 vector registers, so that two workgroups (eight
 // waves per SIMD) share a compute unit when there are many heads; left to itself the register allocator
 // takes more for them as soon as unrelated code of the general instantiations changes.
-template <int MODE, int PLAIN>
+template <int MODE, int PLAIN, int BATCH>
 __global__ __launch_bounds__(kFinThreads, PLAIN == 2 ? 8 : 4) void finalize_kernel(FinArgs a) {
   extern __shared__ __attribute__((aligned(16))) uint32_t keys[];   // n_pad order-preserving keys (select mode) / pooling stage
   __shared__ float red[kFinWaves];
@@ -277,16 +274,14 @@ __global__ __launch_bounds__(kFinThreads, PLAIN == 2 ? 8 : 4) void finalize_kern
     // Eq. 6 as it stands: a mean of cosines lies in [-1, 1] (down to -2 with the partner counters taken
     // off), so the exponentials need no shift by the maximum
     float s = 0.f;
-    for (int base = 0; base < n; base += kBatch * kFinThreads) {
-      float x[kBatch];
+    for (int i0 = t; i0 < n; i0 += BATCH * kFinThreads) {
+      float x[BATCH];
 #pragma unroll
-      for (int u = 0; u < kBatch; ++u)
-        if (base + u * kFinThreads < n) x[u] = sb[min(base + u * kFinThreads + t, n - 1)];
+      for (int u = 0; u < BATCH; ++u)
+        if (u == 0 || i0 + u * kFinThreads < n) x[u] = sb[i0 + u * kFinThreads];
 #pragma unroll
-      for (int u = 0; u < kBatch; ++u) {
-        if (base + u * kFinThreads >= n) break;
-        s = base + u * kFinThreads + t < n ? s + __expf(x[u]) : s;
-      }
+      for (int u = 0; u < BATCH; ++u)
+        if (u == 0 || i0 + u * kFinThreads < n) s += __expf(x[u]);
     }
     sinv = 1.0f / block_sum(s, red);
   }
@@ -451,38 +446,41 @@ __global__ __launch_bounds__(kFinThreads, PLAIN == 2 ? 8 : 4) void finalize_kern
   }
 
   // ---- per-candidate redundancy and joint score
-  const float* imp_src = nullptr;
-  const float* red_src = nullptr;
-  if constexpr ((MODE & kModeZ) != 0) {
-    imp_src = (MODE & kModeImportance) != 0 ? imp_dst : a.imp_in + (int64_t)head * a.imp_stride;
-    if constexpr ((MODE & kModeRedundancy) == 0) red_src = a.red_in ? a.red_in + (int64_t)head * n : nullptr;   // none: attention-only score
-  }
-  for (int base = 0; base < n; base += kBatch * kFinThreads) {
-    float imp[kBatch], sim[kBatch], red[kBatch];
+  // (an importance that was formed beside the similarity pass lies in the workspace's rows, a caller's one is dense)
+  auto importance_of = [&](int i) __attribute__((always_inline)) -> float {
+    if constexpr ((MODE & kModeZ) == 0) return 0.f;
+    else if constexpr ((MODE & kModeImportance) != 0) return imp_dst[i];
+    else return a.imp_in[(int64_t)head * ((MODE & kModeRedundancy) != 0 ? a.n_pad : n) + i];
+  };
+  auto finish = [&](int i, float imp, float s) __attribute__((always_inline)) {
+    float rd = 0.f;
+    if constexpr ((MODE & kModeRedundancy) != 0) {
+      rd = __expf(s) * sinv;
+      if (a.red_out) a.red_out[(int64_t)head * n + i] = rd;
+      if (a.sbar_out) a.sbar_out[(int64_t)head * n + i] = s;
+    } else if constexpr ((MODE & kModeZ) != 0) {
+      rd = a.red_in ? a.red_in[(int64_t)head * n + i] : 0.f;      // no redundancy input: attention-only score
+    }
+    if constexpr ((MODE & kModeZ) != 0) {
+      const float z = a.lambda * imp - (1.0f - a.lambda) * rd;
+      if (a.score_out) a.score_out[(int64_t)head * n + i] = z;
+      if constexpr ((MODE & kModeScore) != 0) a.z_tmp[(int64_t)head * a.n_pad + i] = z;
+      else keys[i] = order_key(z);
+    }
+  };
+  for (int i0 = t; i0 < n; i0 += BATCH * kFinThreads) {
+    float imp[BATCH], sim[BATCH];
 #pragma unroll
-    for (int u = 0; u < kBatch; ++u) {
-      if (base + u * kFinThreads >= n) break;
-      const int i = min(base + u * kFinThreads + t, n - 1);
-      imp[u] = (MODE & kModeZ) != 0 ? imp_src[i] : 0.f;
+    for (int u = 0; u < BATCH; ++u) {
+      const int i = i0 + u * kFinThreads;
+      if (u > 0 && i >= n) break;
+      imp[u] = importance_of(i);
       sim[u] = (MODE & kModeRedundancy) != 0 ? sb[i] : 0.f;
-      red[u] = red_src != nullptr ? red_src[i] : 0.f;
     }
 #pragma unroll
-    for (int u = 0; u < kBatch; ++u) {
-      const int i = base + u * kFinThreads + t;
-      if (i >= n) break;
-      float rd = red[u];
-      if constexpr ((MODE & kModeRedundancy) != 0) {
-        rd = __expf(sim[u]) * sinv;
-        if (a.red_out) a.red_out[(int64_t)head * n + i] = rd;
-        if (a.sbar_out) a.sbar_out[(int64_t)head * n + i] = sim[u];
-      }
-      if constexpr ((MODE & kModeZ) != 0) {
-        const float z = a.lambda * imp[u] - (1.0f - a.lambda) * rd;
-        if (a.score_out) a.score_out[(int64_t)head * n + i] = z;
-        if constexpr ((MODE & kModeScore) != 0) a.z_tmp[(int64_t)head * a.n_pad + i] = z;
-        else keys[i] = order_key(z);
-      }
+    for (int u = 0; u < BATCH; ++u) {
+      if (u > 0 && i0 + u * kFinThreads >= n) break;
+      finish(i0 + u * kFinThreads, imp[u], sim[u]);
     }
   }
 
@@ -511,19 +509,25 @@ __global__ __launch_bounds__(kFinThreads) void shared_select_kernel(const float*
   select_and_emit(keys, n, k_sel, alpha, kept + (int64_t)p * H * budget, H, budget, hist, scan_buf, sel);
 }
 
-template <int MODE, int PLAIN>
-hipError_t launch_plain(const FinArgs& a, int heads, size_t lds, hipStream_t stream) {
+template <int MODE, int PLAIN, int BATCH>
+hipError_t launch_batch(const FinArgs& a, int heads, size_t lds, hipStream_t stream) {
   // once per kernel instantiation (initialisation of a function-local static is thread-safe)
-  static const hipError_t configured = hipFuncSetAttribute(reinterpret_cast<const void*>(&finalize_kernel<MODE, PLAIN>),
+  static const hipError_t configured = hipFuncSetAttribute(reinterpret_cast<const void*>(&finalize_kernel<MODE, PLAIN, BATCH>),
                                                            hipFuncAttributeMaxDynamicSharedMemorySize, 32768 * 4);
   if (configured != hipSuccess) return configured;
-  hipLaunchKernelGGL((finalize_kernel<MODE, PLAIN>), dim3(heads), dim3(kFinThreads), lds, stream, a);
+  hipLaunchKernelGGL((finalize_kernel<MODE, PLAIN, BATCH>), dim3(heads), dim3(kFinThreads), lds, stream, a);
   return hipGetLastError();
+}
+
+// The step's own instantiations.
+template <int MODE, int PLAIN>
+hipError_t launch_plain(const FinArgs& a, int heads, size_t lds, hipStream_t stream) {
+  return a.n > kBatchFrom ? launch_batch<MODE, PLAIN, kBatch>(a, heads, lds, stream) : launch_batch<MODE, PLAIN, 1>(a, heads, lds, stream);
 }
 
 template <int MODE>
 hipError_t launch_mode(const FinArgs& a, int heads, size_t lds, hipStream_t stream) {
-  return launch_plain<MODE, 0>(a, heads, lds, stream);
+  return launch_batch<MODE, 0, 1>(a, heads, lds, stream);
 }
 
 }  // namespace
@@ -539,12 +543,7 @@ hipError_t launch_finalize(const Plan& pl, int mode, char* ws,
   a.credit = pl.recency_transposed ? reinterpret_cast<const unsigned long long*>(ws + pl.off_credit) : nullptr;
   a.newer = pl.triangular ? reinterpret_cast<const unsigned long long*>(ws + pl.off_credit) : nullptr;
   a.imp_in = imp_in; a.red_in = red_in;
-  a.imp_stride = pl.n;
-  if (mode == (kModeRedundancy | kModeSelect)) {
-    // formed beside the similarity pass
-    a.imp_in = reinterpret_cast<const float*>(ws + pl.off_imp);
-    a.imp_stride = pl.n_pad;
-  }
+  if (mode == (kModeRedundancy | kModeSelect)) a.imp_in = reinterpret_cast<const float*>(ws + pl.off_imp);   // formed beside the similarity pass
   a.imp_out = imp_out; a.red_out = red_out; a.sbar_out = sbar_out; a.score_out = score_out;
   a.kept = kept_idx;
   a.n = pl.n; a.n_pad = pl.n_pad; a.stat_groups = pl.chunks * (prepass_register_path(pl) ? 4 : 1); a.alpha = pl.alpha; a.W = pl.W;
@@ -582,7 +581,7 @@ hipError_t launch_finalize(const Plan& pl, int mode, char* ws,
   const bool paper_window = pl.alpha == 8 && pl.W == 4;
   if (plain_imp && plain_red && mode == (kModeImportance | kModeRedundancy | kModeSelect)) {
     if (paper_window) return launch_plain<kModeImportance | kModeRedundancy | kModeSelect, 2>(a, pl.heads, lds, stream);
-    return launch_plain<kModeImportance | kModeRedundancy | kModeSelect, 1>(a, pl.heads, lds, stream);
+    return launch_batch<kModeImportance | kModeRedundancy | kModeSelect, 1, 1>(a, pl.heads, lds, stream);
   }
   if (plain_imp && paper_window && default_rule && pl.gram_parts > 1 && mode == (kModeImportance | kModeRedundancy | kModeSelect))
     return launch_plain<kModeImportance | kModeRedundancy | kModeSelect, 3>(a, pl.heads, lds, stream);
@@ -593,7 +592,7 @@ hipError_t launch_finalize(const Plan& pl, int mode, char* ws,
   if (plain_imp && paper_window && mode == (kModeImportance | kModeSelect))       // attention-only eviction
     return launch_plain<kModeImportance | kModeSelect, 2>(a, pl.heads, lds, stream);
   if (plain_imp && paper_window && mode == kModeImportance)                       // the stand-alone importance score
-    return launch_plain<kModeImportance, 2>(a, pl.heads, lds, stream);
+    return launch_batch<kModeImportance, 2, 1>(a, pl.heads, lds, stream);
   switch (mode) {
     case kModeImportance: return launch_mode<kModeImportance>(a, pl.heads, lds, stream);
     case kModeRedundancy: return launch_mode<kModeRedundancy>(a, pl.heads, lds, stream);
