@@ -36,7 +36,7 @@ static constexpr uint32_t kKnownFlags =
 
 static size_t align_up(size_t x) { return (x + 255) & ~(size_t)255; }
 
-rkv_status make_plan(const rkv_params* prm, Plan* pl) {
+rkv_status make_plan(const rkv_params* prm, Plan* pl, bool step) {
   if (prm == nullptr) return RKV_ERR_NULL;
   const rkv_params& q = *prm;
   if (q.num_problems < 0 || q.kv_heads < 1 || q.q_heads < 1 || q.alpha < 1 || q.n_tokens < 1 || q.budget < 1)
@@ -125,9 +125,9 @@ rkv_status make_plan(const rkv_params* prm, Plan* pl) {
   // choose (parts_reserved), so the size query does not depend on the device that is current.
   int parts_reserved = 1;
   {
-    // (counted in row blocks of the dense kernel also for RKV_FLAG_SKIP_SATURATED, whose own row blocks are
-    // smaller: the two must take the same decision, because the split changes the order of the last few
-    // floating-point operations and the flag promises bit-identical results)
+    // (counted in row blocks of the dense kernel also for RKV_FLAG_SKIP_SATURATED, whose own row blocks are smaller.  The flag promises
+    // bit-identical results, and it gets them however the scan is cut: u is summed in the same groups, a row's closed form and its one
+    // forgiven similarity are finished by the same sequence of rounded operations, and products do not depend on the cut)
     const int64_t blocks = (int64_t)pl->heads * ((pl->n + kGramRows - 1) / kGramRows);
     const int nct = (pl->n + kGramTile - 1) / kGramTile;
     pl->gram_parts = 1;
@@ -137,7 +137,8 @@ rkv_status make_plan(const rkv_params* prm, Plan* pl) {
       const int64_t slots = 2 * (int64_t)device_compute_units();
       if (blocks <= slots / 2)
         pl->gram_parts = (int)std::max<int64_t>(1, std::min<int64_t>(parts_reserved, slots / blocks));
-      pl->few = gram_few(pl->heads, pl->n, pl->beta, pl->recency_transposed || pl->triangular || pl->skip_saturated);
+      const bool beside = step && pl->lambda != 1.0f && early_importance(*pl);
+      pl->few = gram_few(pl->heads, pl->n, pl->beta, beside, pl->recency_transposed || pl->triangular || pl->skip_saturated);
       if (pl->few) pl->gram_parts = nct;
     }
   }
@@ -294,7 +295,7 @@ static rkv_status compress_impl(const rkv_params* prm, const void* q_obs, const 
                                 void* k_out, void* v_out, int32_t* kept_idx, float* score,
                                 void* ws, size_t ws_bytes, void* stream, void* const* events, bool inplace = false) {
   Plan pl;
-  rkv_status s = make_plan(prm, &pl);
+  rkv_status s = make_plan(prm, &pl, true);
   if (s != RKV_OK) return s;
   if (empty(pl)) return RKV_OK;
   if (q_obs == nullptr || k == nullptr || v == nullptr) return RKV_ERR_NULL;

@@ -93,13 +93,22 @@ RKV_HD GramHandover gram_handover(int heads, int row_blocks, int n, float T, int
 }
 
 // Few heads: 128 rows against one column tile a workgroup (gram_few.hip), where a head has at most 16 tiles (so many reports a row
-// the finalize kernel merges at once) and the workgroups, four to a compute unit, make about a round and a half at most.  A whole
-// step, us, blocks of 384 rows / this, T = 0.5 repeated text, T = 0.5 noisy copies, T = 0.95: 2 heads of n = 376 25.1 / 20.2, 26.1 / 20.4,
-// 22.9 / 20.3; 8 of n = 1144 (648 workgroups) 29.2 / 26.7, 29.1 / 26.4, 27.2 / 26.1; 64 of n = 632 (1600) 38.9 / 34.8, 41.0 / 34.4,
-// 36.5 / 34.5; 8 of n = 2032 (2048) 36.5 / 36.0, 39.3 / 36.2, 33.7 / 35.8; 16 of n = 1632 (2704) 39.7 / 39.6, 43.4 / 40.0, 37.1 / 40.1.
-RKV_HD bool gram_few(int heads, int n, int beta, bool other) {
+// the finalize kernel merges at once) and the workgroups, four to a compute unit, make about a round and a half at most.
+// It gains where rows have partners, which the other launch's workgroups of 384 rows spend their time on.  It costs a little where there are
+// none and its workgroups need another round of the one XCD that a head's lie on (which is also why one head costs what eight do).  Time of
+// the other launch over this one's; keys of repeated text / noisy copies / 256 clusters at T = 0.5, repeated text / clusters at T = 0.95 /
+// independent keys:
+//   a step    1 head,  n = 384 1.23 1.31 1.35 / 1.18 1.25 / 1.10, 1152 1.11 1.12 1.14 / 1.01 1.09 / 0.98, 2048 1.12 1.11 1.17 / 0.99 1.09 / 0.94
+//             8 heads, n = 640 1.24 1.25 1.28 / 1.16 1.21 / 1.08, 1152 1.10 1.11 1.13 / 1.01 1.10 / 0.99, 1792 1.07 1.12 1.21 / 1.00 1.10 / 0.95
+//             16, n = 1152 1.05 1.07 1.09 / 0.96 1.04 / 0.96; 64, n = 640 1.11 1.20 1.26 / 1.04 1.16 / 1.00; 256, n = 192 1.00 1.02 1.02 / 1.00 1.01 / 0.97
+//   the pass  8 heads, n = 1024 1.20 1.22 1.26 / 1.06 1.19 / 0.99, 1792 1.12 1.18 1.31 / 0.99 1.15 / 0.92; 96, n = 384 1.19 1.25 1.28 / 1.09 1.17 / 1.02
+//   alone     132, n = 384 1.07 1.12 1.12 / 0.98 1.07 / 0.91; 160, n = 384 1.01 1.05 1.05 / 0.92 1.00 / 0.86; 256, n = 192 0.94 0.99 0.99 / 0.94 0.96 / 0.85
+// (T = 0.95 draws no line: repeated text, whose noise is just above it, is even there or 4 % slower, noisy copies and clusters 4 to 16 %
+// faster.)  With more than 128 heads, of two or three tiles then, the pass alone is the slower one; a step (`beside`: it forms the
+// importance in the same launch) is not.
+RKV_HD bool gram_few(int heads, int n, int beta, bool beside, bool other) {
   const int tiles = (n + 127) / 128;
-  return beta == 1 && !other && tiles > 1 && tiles <= 16 && (long long)heads * tiles * tiles <= 1700;
+  return beta == 1 && !other && tiles > 1 && tiles <= 16 && (long long)heads * tiles * tiles <= 1700 && (beside || heads <= 128);
 }
 
 // An open row, as it is listed: the row and the subtile of 32 keys below which it is still to be compared.

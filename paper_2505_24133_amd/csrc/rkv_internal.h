@@ -84,7 +84,8 @@ struct Plan {
   size_t total;
 };
 
-rkv_status make_plan(const rkv_params* prm, Plan* plan);
+// `step`: for the whole step (the similarity pass may have the importance beside it), else for one of its parts.  The workspace is the same.
+rkv_status make_plan(const rkv_params* prm, Plan* plan, bool step = false);
 // Who takes the last open rows of the similarity pass's row blocks (gram_index.h has the rule).
 inline GramHandover handover(const Plan& pl) {
   return gram_handover(pl.heads, (pl.n + kGramRows - 1) / kGramRows, pl.n, pl.T, pl.beta, pl.gram_parts,

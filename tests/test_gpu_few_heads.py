@@ -25,12 +25,13 @@ def _keys(P, H, N, clusters, seed):
     pytest.param(8, 8, 640, 20, 0.95, 0, id="1600 workgroups, T above 0.9"),
     pytest.param(1, 6, 2048, 300, 0.45, 0, id="sixteen tiles"),
     pytest.param(1, 8, 1800, 1, 0.45, 0, id="every row a partner of every other"),
+    pytest.param(33, 4, 384, 30, 0.45, 0, id="132 heads: in the step, not in the pass alone"),
 ])
 def test_one_tile_a_workgroup(P, H, n, clusters, T, page):
     print(f"[gpu-case] few heads P={P} H={H} n={n} clusters={clusters} T={T} page={page}", flush=True)
     N = n + 8
     k, gen = _keys(P, H, N, clusters, n)
-    shape = rkv.Shape(num_problems=P, kv_heads=H, q_heads=H, n_tokens=N, budget=N - 64, sim_threshold=T)
+    shape = rkv.Shape(num_problems=P, kv_heads=H, q_heads=H, n_tokens=N, budget=N - 64, sim_threshold=T, lam=0.5)
     stored = k
     if page:
         per = -(-N // page)
@@ -40,7 +41,11 @@ def test_one_tile_a_workgroup(P, H, n, clusters, T, page):
         stored = torch.empty((P * per, H, page, 128), dtype=torch.bfloat16, device="cuda")
         stored[table.reshape(-1).long()] = rows.view(P, H, per, page, 128).transpose(1, 2).reshape(P * per, H, page, 128)
         shape.page_size, shape.block_table = page, table
-    _, mean = rkv.rkv_score_redundancy(shape, stored, want_mean_sim=True)
+    q = torch.randn((P, H, 8, 128), generator=gen, device="cuda").bfloat16()
+    _, _, _, kept, score = rkv.rkv_compress(shape, q, stored, stored, want_score=True)
+    red, mean = rkv.rkv_score_redundancy(shape, stored, want_mean_sim=True)
+    kept2, score2 = rkv.rkv_select_topk(shape, rkv.rkv_score_importance(shape, q, stored), red, want_score=True)
+    assert torch.equal(score, score2) and torch.equal(kept, kept2)
     shape.flags = rkv.RKV_FLAG_SKIP_SATURATED             # row blocks of 256 rows, the same products in the same order
     assert torch.equal(mean, rkv.rkv_score_redundancy(shape, stored, want_mean_sim=True)[1])
     unit = torch.nn.functional.normalize(k[P - 1, H - 1, :n].double(), dim=-1)
