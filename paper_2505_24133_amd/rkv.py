@@ -65,7 +65,7 @@ class RkvError(RuntimeError):
 
 
 _lib = None
-_append = None               # _host.append, once the library is loaded
+_append = None               # _host.append once the library is loaded, or a function that takes no call if that module does not load
 
 
 def load_library() -> ctypes.CDLL:
@@ -96,13 +96,15 @@ def load_library() -> ctypes.CDLL:
         getattr(lib, name).restype = ctypes.c_int
     lib.rkv_status_string.argtypes = [ctypes.c_int]
     lib.rkv_status_string.restype = ctypes.c_char_p
+    global _append
     try:
         from . import _host
-    except ImportError as e:
-        raise RuntimeError(f"the native host module is missing or does not load ({e}): build it with `python -m paper_2505_24133_amd.build`") from e
-    _host.bind(ctypes.cast(lib.rkv_cache_append, ctypes.c_void_p).value)
-    global _append
-    _append = _host.append
+    except ImportError:
+        # built for another Python or torch, or not at all: no call is taken, every append goes through ctypes
+        _append = lambda *args: None  # noqa: E731
+    else:
+        _host.bind(ctypes.cast(lib.rkv_cache_append, ctypes.c_void_p).value)
+        _append = _host.append
     _lib = lib
     return lib
 

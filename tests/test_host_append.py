@@ -1,10 +1,13 @@
 """The native host path of an appended token: what it takes gives the bytes of the plain call through ctypes, what it does not take is left
 to the binding's own checks, with their errors."""
 import ctypes
+import subprocess
+import sys
 
 import pytest
 import torch
 
+import paper_2505_24133_amd
 from paper_2505_24133_amd import rkv
 
 
@@ -42,6 +45,33 @@ def test_calls_that_are_not_taken():
         rkv._append(s, *good)
     with pytest.raises(RuntimeError, match="GPU tensors only"):
         rkv.rkv_cache_append(s, *good, 0, 0)
+
+
+def _without_host(code, repo_root):
+    """Runs `code` in a fresh interpreter in which the native host module does not load."""
+    start = "import sys; sys.modules['paper_2505_24133_amd._host'] = None; import torch; from paper_2505_24133_amd import rkv; "
+    r = subprocess.run([sys.executable, "-c", start + code], cwd=repo_root, capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr
+    return r.stdout
+
+
+def test_the_library_works_without_the_host_module(repo_root):
+    assert int(_without_host("print(rkv.rkv_workspace_size(rkv.Shape(2, 2, 6, 40, 24)))", repo_root)) == rkv.rkv_workspace_size(_shape())
+    assert _without_host("rkv.load_library(); print(rkv._append(rkv.Shape(2, 2, 6, 40, 24), 0, 0, 0, 0, 0, 0, 0, 0))", repo_root) == "None\n"
+
+
+@pytest.mark.gpu
+def test_an_append_without_the_host_module(monkeypatch):
+    print("[gpu-case] append without the host module", flush=True)
+    monkeypatch.setitem(sys.modules, "paper_2505_24133_amd._host", None)
+    monkeypatch.delattr(paper_2505_24133_amd, "_host", raising=False)
+    monkeypatch.setattr(rkv, "_lib", None)
+    monkeypatch.setattr(rkv, "_append", None)
+    s = _shape()
+    t = _tensors(s, "cuda")
+    rkv.rkv_cache_append(s, *t, 11, 4)
+    assert rkv._append(s, *t, 0, 0) is None
+    assert torch.equal(t[0][:, :, 11], t[3]) and torch.equal(t[1][:, :, 11], t[4]) and torch.equal(t[2][:, :, 4], t[5])
 
 
 @pytest.mark.gpu
