@@ -3,8 +3,8 @@
 // Python 9.8 us an append (one sequence of 32 layers, DecodeCache.append), now 4.1, most of it the launch; 128 appends and the
 // compression behind them 993 us, now 544.
 //
-// append() takes a call whose arguments are all in order and enqueues it; anything else (another type, layout, device, a paged
-// cache, a value out of an int's range) it does not touch and answers None, and the Python binding goes through its own checks.
+// append() takes a call whose arguments are all in order and enqueues it; anything else (another type, a subclass of the shape or of a
+// tensor, another layout or device, a paged cache, a value out of an int's range) it does not touch and answers None, and the Python binding goes through its own checks.
 #include <Python.h>
 
 #include <ATen/core/Tensor.h>
@@ -18,6 +18,7 @@ namespace {
 
 using AppendFn = rkv_status (*)(const rkv_params*, void*, void*, void*, const void*, const void*, const void*, int32_t, int32_t, void*);
 AppendFn append_fn = nullptr;
+PyObject* shape_type = nullptr;    // rkv.Shape
 
 enum Field { kProblems, kKvHeads, kQHeads, kTokens, kBudget, kAlpha, kHeadDim, kPoolW, kBeta, kThreshold, kLam, kEps, kFlags, kPageSize, kFields };
 const char* const kNames[kFields] = {"num_problems", "kv_heads", "q_heads", "n_tokens", "budget", "alpha", "head_dim",
@@ -63,7 +64,8 @@ PyObject* append(PyObject*, PyObject* const* args, Py_ssize_t count) {
     constexpr int64_t kMax = INT32_MAX;
     int64_t n[kFields] = {};
     rkv_params p = {};
-    bool ok = append_fn != nullptr;
+    // (a subclass may fill the parameter block in its own way)
+    bool ok = append_fn != nullptr && (PyObject*)Py_TYPE(shape) == shape_type;
     for (Field f : {kProblems, kKvHeads, kQHeads, kTokens, kBudget, kAlpha, kHeadDim, kPoolW, kBeta}) ok = ok && int_field(shape, f, -kMax - 1, kMax, &n[f]);
     ok = ok && int_field(shape, kFlags, 0, UINT32_MAX, &n[kFlags]) && int_field(shape, kPageSize, 0, 0, &n[kPageSize]);
     ok = ok && float_field(shape, kThreshold, &p.sim_threshold) && float_field(shape, kLam, &p.lambda) && float_field(shape, kEps, &p.eps);
@@ -104,18 +106,23 @@ PyObject* append(PyObject*, PyObject* const* args, Py_ssize_t count) {
   }
 }
 
-// The address of rkv_cache_append in the loaded library.
-PyObject* bind(PyObject*, PyObject* address) {
+// The address of rkv_cache_append in the loaded library and the class of its shapes.
+PyObject* bind(PyObject*, PyObject* args) {
+  PyObject *address, *type;
+  if (!PyArg_ParseTuple(args, "OO!", &address, &PyType_Type, &type)) return nullptr;
   void* p = PyLong_AsVoidPtr(address);
   if (p == nullptr && PyErr_Occurred()) return nullptr;
   append_fn = reinterpret_cast<AppendFn>(p);
+  Py_INCREF(type);
+  Py_XDECREF(shape_type);
+  shape_type = type;
   Py_RETURN_NONE;
 }
 
 PyMethodDef methods[] = {
     {"append", reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)()>(append)), METH_FASTCALL,
      "append(shape, k_cache, v_cache, q_cache, k_new, v_new, q_new, position, slot) -> status, or None if the call is not taken"},
-    {"bind", bind, METH_O, "bind(address of rkv_cache_append)"},
+    {"bind", bind, METH_VARARGS, "bind(address of rkv_cache_append, class of the shapes)"},
     {nullptr, nullptr, 0, nullptr}};
 PyModuleDef module = {PyModuleDef_HEAD_INIT, "_host", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};
 

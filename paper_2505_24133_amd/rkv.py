@@ -103,7 +103,7 @@ def load_library() -> ctypes.CDLL:
         # built for another Python or torch, or not at all: no call is taken, every append goes through ctypes
         _append = lambda *args: None  # noqa: E731
     else:
-        _host.bind(ctypes.cast(lib.rkv_cache_append, ctypes.c_void_p).value)
+        _host.bind(ctypes.cast(lib.rkv_cache_append, ctypes.c_void_p).value, Shape)
         _append = _host.append
     _lib = lib
     return lib

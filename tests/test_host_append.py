@@ -114,6 +114,32 @@ def test_stream_and_refusals():
             rkv.rkv_cache_append(s, *wrong, 0, 0)
     rkv.rkv_cache_append(s, *t, torch.tensor(6), 2)                           # not an int: the binding's own way
     assert torch.equal(t[0][:, :, 6], t[3])
-    same = torch.nn.Parameter(t[3], requires_grad=False)                      # nor a plain tensor
+    same = t[3].as_subclass(_Wrapped)                                         # nor a plain tensor
+    assert rkv._append(s, t[0], t[1], t[2], same, t[4], t[5], 8, 2) is None
     rkv.rkv_cache_append(s, t[0], t[1], t[2], same, t[4], t[5], 8, 2)
     assert torch.equal(t[0][:, :, 8], t[3])
+
+
+class _Wrapped(torch.Tensor):
+    pass
+
+
+class _Refusing(rkv.Shape):
+    """A shape that fills the parameter block in its own way."""
+
+    def params(self, *args, **kw):
+        p = super().params(*args, **kw)
+        p.head_dim = 64
+        return p
+
+
+@pytest.mark.gpu
+def test_a_shape_of_another_class_is_asked_for_its_parameters():
+    print("[gpu-case] host append shape subclass", flush=True)
+    rkv.load_library()
+    s = _Refusing(**{k: v for k, v in vars(_shape()).items()})
+    t = _tensors(s, "cuda")
+    before = t[0].clone()
+    with pytest.raises(rkv.RkvError) as e:
+        rkv.rkv_cache_append(s, *t, 5, 1)
+    assert e.value.status == rkv.RKV_ERR_UNSUPPORTED and torch.equal(t[0], before)
