@@ -2,6 +2,7 @@
 from __future__ import annotations
 
 import os
+import shutil
 import subprocess
 import sys
 import sysconfig
@@ -28,6 +29,15 @@ def _compile(src: str) -> str:
     return obj
 
 
+def rocm_include() -> str:
+    """The headers of the ROCm that hipcc belongs to: ROCM_PATH's if it is set, else those beside the hipcc found in PATH."""
+    root = os.environ.get("ROCM_PATH")
+    if not root:
+        hipcc = shutil.which("hipcc")
+        root = os.path.dirname(os.path.dirname(os.path.realpath(hipcc))) if hipcc else "/opt/rocm"
+    return os.path.join(root, "include")
+
+
 def _build_host() -> None:
     import torch
 
@@ -35,7 +45,7 @@ def _build_host() -> None:
     lib = os.path.join(base, "lib")
     cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-DUSE_ROCM", "-D__HIP_PLATFORM_AMD__",
            f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
-           "-I", os.path.join(ROOT, "include"), "-I", os.path.join(base, "include"), "-I", "/opt/rocm/include",
+           "-I", os.path.join(ROOT, "include"), "-I", os.path.join(base, "include"), "-I", rocm_include(),
            "-I", sysconfig.get_paths()["include"], os.path.join(CSRC, "host.cpp"), "-o", HOST,
            "-L", lib, "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip", f"-Wl,-rpath,{lib}"]
     r = subprocess.run(cmd, capture_output=True, text=True)

@@ -14,9 +14,9 @@ def recorder(repo_root, tmp_path_factory):
     if not os.path.exists(B.LIB):
         B.build()
     exe = str(tmp_path_factory.mktemp("launches") / "launch_record")
-    subprocess.run(["g++", "-O1", "-Wall", "-D__HIP_PLATFORM_AMD__", "-I", os.path.join(repo_root, "include"), "-I", "/opt/rocm/include",
-                    os.path.join(repo_root, "tests", "launch_record.cpp"), "-o", exe, "-rdynamic", B.LIB, "-L/opt/rocm/lib", "-lamdhip64",
-                    f"-Wl,-rpath,{os.path.dirname(B.LIB)}:/opt/rocm/lib"], check=True)
+    subprocess.run(["g++", "-O1", "-Wall", "-D__HIP_PLATFORM_AMD__", "-I", os.path.join(repo_root, "include"), "-I", B.rocm_include(),
+                    os.path.join(repo_root, "tests", "launch_record.cpp"), "-o", exe, "-rdynamic", B.LIB, "-L" + os.path.join(os.path.dirname(B.rocm_include()), "lib"), "-lamdhip64",
+                    f"-Wl,-rpath,{os.path.dirname(B.LIB)}:{os.path.join(os.path.dirname(B.rocm_include()), 'lib')}"], check=True)
     return exe
 
 
