@@ -487,16 +487,22 @@ void launch_paged(const PrepassArgs& a, hipStream_t stream) {
   hipLaunchKernelGGL((prepass_kernel<HAS_Q, MT, AH, PAGED>), grid, block, 0, stream, a);
 }
 
-// As many workgroups as stay resident at once, or fewer if an even share of the chunks needs fewer.
+// Workgroups of it that stay resident at once (queried once).
 template <int AH>
-void launch_dma(const PrepassArgs& a, hipStream_t stream) {
+int dma_resident() {
   static const int res = [] {
     int per_cu = 0;
     const void* fn = reinterpret_cast<const void*>(&prepass_dma_kernel<AH>);
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, kPrepassThreads, 0) != hipSuccess || per_cu < 1) per_cu = 2;
     return per_cu * device_compute_units();
   }();
-  const int64_t chunks_x = (int64_t)((a.items / a.chunks + 7) / 8) * a.chunks, fit = std::max(1, res / 8);
+  return res;
+}
+
+// As many workgroups as stay resident at once, or fewer if an even share of the chunks needs fewer.
+template <int AH>
+void launch_dma(const PrepassArgs& a, hipStream_t stream) {
+  const int64_t chunks_x = (int64_t)((a.items / a.chunks + 7) / 8) * a.chunks, fit = std::max(1, dma_resident<AH>() / 8);
   const int64_t rounds = (chunks_x + fit - 1) / fit;
   hipLaunchKernelGGL((prepass_dma_kernel<AH>), dim3((unsigned)(8 * ((chunks_x + rounds - 1) / rounds))), dim3(kPrepassThreads), 0, stream, a);
 }
@@ -508,11 +514,6 @@ void launch_variant(const PrepassArgs& a, hipStream_t stream) {
 }
 
 }  // namespace
-
-// Chunks enough for eight a workgroup: from there on the copies in flight behind the logits pay.  Where a workgroup has one to four,
-// reading a chunk back from LDS costs its latency (one layer of the 8B shape 4.9 -> 5.7 us); with one row tile of queries both run
-// at the same 4.9 TB/s, writes included (1024 heads of n = 8312 548 / 522 us in a trace, the whole step within 1 %).
-static bool prepass_by_dma(int items) { return items >= 8 * 768; }
 
 int prepass_register_path(const Plan& pl) {
   const bool usual = pl.alpha == 8 || pl.alpha == 16 || pl.alpha == 32;
@@ -548,7 +549,7 @@ hipError_t launch_prepass(const Plan& pl, const void* q_obs, const void* k, char
   else if (fast == 4) launch_variant<true, 1, 4>(a, stream);
   else if (fast == 8) launch_variant<true, 1, 8>(a, stream);
   else if (fast == 16) launch_variant<true, 1, 16>(a, stream);
-  else if (fast == 104 && a.table == nullptr && prepass_by_dma(a.items)) launch_dma<4>(a, stream);
+  else if (fast == 104 && a.table == nullptr && prepass_by_dma(a.items, dma_resident<4>())) launch_dma<4>(a, stream);
   else if (fast == 104) launch_variant<true, 2, 4>(a, stream);
   else if (fast == 108) launch_variant<true, 2, 8>(a, stream);
   else if (pl.G * pl.alpha <= 32) launch_variant<true, 1, 0>(a, stream);

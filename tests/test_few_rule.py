@@ -14,7 +14,15 @@ def rule(repo_root, tmp_path_factory):
 
     def ask(heads, n, beta=1, beside=True, other=False):
         return subprocess.run([exe, *map(str, (heads, n, beta, int(beside), int(other)))], capture_output=True, text=True, check=True).stdout == "1"
+    ask.exe = exe
     return ask
+
+
+def test_copies_ahead_in_the_prepass(rule):
+    """Eight chunks a resident workgroup, whatever the device holds."""
+    def ask(*args):
+        return subprocess.run([rule.exe, *map(str, args)], capture_output=True, text=True, check=True).stdout == "1"
+    assert ask(6144, 768) and not ask(6143, 768) and ask(2432, 304) and not ask(6144, 1024)
 
 
 def test_a_step(rule):
