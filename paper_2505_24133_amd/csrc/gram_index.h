@@ -92,15 +92,15 @@ RKV_HD GramHandover gram_handover(int heads, int row_blocks, int n, float T, int
   return (long long)heads * row_blocks * n * 256 <= 500000000ll ? kOwnTail : kListTail;
 }
 
-// Whether the pre-pass copies its chunks to LDS ahead (prepass_dma_kernel): two row tiles of queries, a contiguous cache
-// and chunks for eight a workgroup, with `resident` workgroups at a time (768 on the 256 compute units of an
+// Whether the pre-pass copies its chunks to LDS ahead (prepass_dma_kernel): two row tiles of queries, a contiguous cache of 16-byte aligned
+// rows (what its copies move) and chunks for eight a workgroup, with `resident` workgroups at a time (768 on the 256 compute units of an
 // MI355X).  Chunks a workgroup, us of the stand-alone importance without / with it, 40 query rows and n = 2168: 1.1 17.2 / 18.5, 3 31.2 / 31.4,
 // 4.1 38.5 / 37.0, 6 52.4 / 48.1, 8 63.9 / 54.7, 10 84.7 / 70.9, 16 140 / 123, 32 273 / 241; 64 query rows, 1.1 18.7 / 20.1, 4.1 42.6 / 38.7,
 // 8 72.5 / 57.0; n = 512, 40 query rows, 8 69.1 / 61.7.  Reading a chunk back from LDS costs its latency, which the copies in flight pay for
 // from about four a workgroup on; from eight on it is ahead by a tenth and more at every size.
 // With one row tile of queries both run at the same 4.9 TB/s, writes included (1024 heads of n = 8312 548 / 522 us in a trace, the whole step
 // within 1 %).  Windows of 16 with two row tiles, and paged caches, have not been built this way.
-RKV_HD bool prepass_by_dma(int chunks, int resident) { return (long long)chunks >= 8ll * resident; }
+RKV_HD bool prepass_by_dma(int chunks, int resident, bool aligned) { return aligned && (long long)chunks >= 8ll * resident; }
 
 // Few heads: 128 rows against one column tile a workgroup (gram_few.hip), where a head has at most 16 tiles (so many reports a row
 // the finalize kernel merges at once) and the workgroups, four to a compute unit, make about a round and a half at most.

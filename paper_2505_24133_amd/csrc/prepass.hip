@@ -549,7 +549,7 @@ hipError_t launch_prepass(const Plan& pl, const void* q_obs, const void* k, char
   else if (fast == 4) launch_variant<true, 1, 4>(a, stream);
   else if (fast == 8) launch_variant<true, 1, 8>(a, stream);
   else if (fast == 16) launch_variant<true, 1, 16>(a, stream);
-  else if (fast == 104 && a.table == nullptr && prepass_by_dma(a.items, dma_resident<4>())) launch_dma<4>(a, stream);
+  else if (fast == 104 && a.table == nullptr && prepass_by_dma(a.items, dma_resident<4>(), ((uintptr_t)a.k & 15) == 0)) launch_dma<4>(a, stream);
   else if (fast == 104) launch_variant<true, 2, 4>(a, stream);
   else if (fast == 108) launch_variant<true, 2, 8>(a, stream);
   else if (pl.G * pl.alpha <= 32) launch_variant<true, 1, 0>(a, stream);

@@ -19,10 +19,11 @@ def rule(repo_root, tmp_path_factory):
 
 
 def test_copies_ahead_in_the_prepass(rule):
-    """Eight chunks a resident workgroup, whatever the device holds."""
+    """Eight chunks a resident workgroup, whatever the device holds, and rows that 16-byte copies can read."""
     def ask(*args):
         return subprocess.run([rule.exe, *map(str, args)], capture_output=True, text=True, check=True).stdout == "1"
-    assert ask(6144, 768) and not ask(6143, 768) and ask(2432, 304) and not ask(6144, 1024)
+    assert ask(6144, 768, 1) and not ask(6143, 768, 1) and not ask(1 << 24, 768, 0)
+    assert ask(2432, 304, 1) and not ask(6144, 1024, 1)
 
 
 def test_a_step(rule):
