@@ -3,10 +3,9 @@
 // in flight on a compute unit are its 32 waves.  Pure HBM traffic; the stores are non-temporal (the
 // compacted rows are not read again by this step, and keeping them out of the caches is worth 15 % of
 // the kernel's time).
-// One row a thread instead of four whose indices (and pages) were asked for one after the other, us: 256 heads, budget 1024
-// 39.1 -> 38.8, 4096 180 -> 177, paged 2048 121 -> 92, 2 heads of 256 4.6 -> 2.8; two or four rows with all indices
-// first lie between.  With non-temporal loads where the caches are too small (gather_streams): 4096 177 -> 151, paged 92 -> 83, 6144
-// heads of 2048 2313 -> 2166 to 2310 (where the buffers lie decides; 5.6 to 5.9 TB/s read and written), 1024 of 8192 1503 -> 1420.
+// One row a thread instead of four whose indices (and pages) were asked for one after the other, us of the gather alone: 256 heads,
+// budget 1024 39.1 -> 38.8, 4096 180 -> 177, paged 2048 121 -> 92, 2 heads of 256 4.6 -> 2.8; two or four rows with all indices
+// first lie between.
 #include <algorithm>
 
 #include "rkv_internal.h"
@@ -65,8 +64,12 @@ __global__ __launch_bounds__(kGatherThreads) void gather_kernel(GatherArgs a) {
   __builtin_nontemporal_store(vr, reinterpret_cast<u32x4*>(a.v_out + o));
 }
 
-// Caches too large for the 256 MB behind the L2s are read past it: the pre-pass's keys are long gone from there and nothing reads
-// these rows again.  Below that the keys are still there (256 heads of n = 1152, 150 MB of K and V: 38.8 us, non-temporal 39.9).
+// Caches that the 256 MB behind the L2s cannot hold are read past it: the pre-pass's keys are gone from there and nothing reads these
+// rows again.  K and V, us, ordinary / non-temporal loads, behind the other kernels of an attention-only step: 180 MiB 83 / 88, 252 114 / 116,
+// 288 127 / 129, 325 170 / 170, 360 168 / 164, paged (a dense copy of the keys is in the way, too) 180 106 / 104, 252 148 / 140, 288 168 / 159,
+// 360 225 / 210; a whole step of 256 heads of n = 4216 (1.1 GB) 431 / 406, of 256 MB paged 240 / 230, of 6144 heads of n = 2168 (6.8 GB)
+// 4749 / 4657, of 1024 of n = 8312 3131 / 3081.  Between 256 and 330 MiB a contiguous cache would still do better from there, by 1 % of a step
+// and a tenth of the gather by itself.
 bool gather_streams(const Plan& pl) { return (int64_t)pl.heads * pl.N * kRowBytes * 2 > (256ll << 20); }
 
 }  // namespace

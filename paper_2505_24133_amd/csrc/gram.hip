@@ -63,9 +63,9 @@ enum GramVariant : int { kPlain = 0, kSplit = 1, kTransposed = 2, kTriangular = 
 // Once no more than 1 / kHandoverShare of a block's rows are open, the block leaves the scan, and its open rows are taken
 // against the keys that are left by tail_group: by the block itself (kOwnTail), or, where many heads have long scans,
 // together with the other blocks' open rows by gram_tail_kernel (kListTail).
-// Measured, us, full scan -> scan with hand-over (+ tail kernel), repeated text at T = 0.5: 256 heads of n = 1144 76 -> 40, of
-// n = 4216 858 -> 73 + 95; 6144 heads of n = 2168 5796 -> 871 + 602 (4.1 and 5.8 TB/s past the L2s, a copy reaches 5.4);
-// 1024 heads of n = 8312, 64 clusters, 13152 -> 618 + 310.
+// Measured, us, full scan -> scan with hand-over (+ tail kernel), repeated text at T = 0.5: 256 heads of n = 1144 76 -> 41, of
+// n = 4216 858 -> 94 + 96 (both with the importance in the scan's launch); 6144 heads of n = 2168 5796 -> 850 + 605 (4.1 and
+// 5.8 TB/s past the L2s, a copy reaches 5.4); 1024 heads of n = 8312, 64 clusters, 13152 -> 599 + 317.
 // A quarter: at an eighth blocks with a fifth of their rows alone never leave (redundancy of 256 heads of n = 4216 401 -> 895 us,
 // full scan 890); at a half the tail, whose rows cost more, has too many (8 heads of n = 32760 934 -> 1145).
 // Where no row meets a partner the full scan runs with what the hand-over adds: the looks, and one memory latency for the
@@ -335,7 +335,7 @@ __global__ __launch_bounds__(NW * 64, WPS) void gram_kernel(GramArgs a) {
     dma16(kbase, (uint32_t)key * row_bytes + (uint32_t)lane_chunk * 16u, (uint32_t)__builtin_amdgcn_readfirstlane((int)dst));
   };
   // Unclamped form, used inside the scan: per tile one scalar source pointer (the wave's first row of the
-  // tile) and one scalar LDS address; the wave's copies lie 16 rows apart in both.
+  // tile) and one scalar LDS address; the wave's copies lie 16 rows apart in LDS, and in memory too, or by turns 8 and 24 rows (HALVES).
   const uint32_t lane_off = (uint32_t)gram_copy_lane_row(lane, n) * row_bytes + (uint32_t)lane_chunk * 16u;
   const uint32_t group_step = (uint32_t)gram_copy_group_row(HALVES ? halves_copy_row(1) : 16, TC, n) * row_bytes;
   auto tile_source = [&](int ct) -> uint64_t {

@@ -1,8 +1,13 @@
 // The importance of a head's candidates (Eq. 3-4) as extra workgroups of the similarity pass's launch.  It needs the pre-pass
 // only, and where a launch of the finalize kernel has no more than one workgroup per compute unit its importance stage is a chain of
-// latencies on the critical path; beside the similarity pass it costs nothing: finalize, us, 8 heads of n = 1144 11.4 -> 9.0, 8 heads of
-// n = 32760 124 -> 77; a whole step 2 to 4 us less up to 64 heads, one sequence of 32 layers 117.6 -> 113.8.  (With thousands of heads the finalize kernel's 32 waves a compute unit
-// read the logits faster than the eight that fit beside the similarity pass.)
+// latencies on the critical path.  Beside the similarity pass it fills what that launch leaves idle, and lengthens it where it leaves
+// nothing: its workgroups come last in the grid, take the LDS of a scan each and read the logits through the same L2s.
+// A step, us, formed by the finalize kernel / here, repeated text at T = 0.5: 2 heads of n = 292 20.7 / 17.8; 8 of n = 1144 26.7 / 23.9, of
+// n = 32760 376 / 334; 64 of n = 1144 60.1 / 57.0; 128 of n = 4216 209.5 / 205.8; 256 of n = 1144 107.0 / 103.4.  Where a step streams its
+// keys from memory several times nothing is left to gain: 256 heads of n = 2168 201.4 / 200.9, of n = 4216 407.0 / 406.2 (the scan's launch
+// 12 longer, the finalize kernel 14 shorter), of n = 8312 1007 / 1008; 224 of n = 4216 353 / 355; 64 of n = 32760 1621 / 1635.
+// Noisy copies at T = 0.95, a long scan: 256 of n = 4216 1105 / 1094, of n = 8312 3734 / 3718.  (With thousands of heads the finalize
+// kernel's 32 waves a compute unit read the logits faster than the eight that fit beside the similarity pass.)
 #pragma once
 
 #include "rkv_internal.h"

@@ -103,8 +103,8 @@ hipError_t launch_prepass(const Plan& pl, const void* q_obs, const void* k, char
 hipError_t launch_gram(const Plan& pl, const void* k, char* ws, bool importance, hipStream_t stream);
 hipError_t launch_gram_few(const Plan& pl, const void* k, char* ws, bool importance, hipStream_t stream);
 
-// Whether the similarity pass's launch can form the importance too: default readings, the paper's window, the schedules whose
-// kernels carry it, and no more heads than compute units.
+// Whether the similarity pass's launch forms the importance too: default readings, the paper's window, the schedules whose kernels carry
+// it, and no more heads than compute units (importance.h has both sides; up to there it gains, or is even within 1 %).
 inline bool early_importance(const Plan& pl) {
   return pl.alpha == 8 && pl.W == 4 && pl.gqa_mode == 0 && !pl.pool_after_mean && !pl.shared_selection && pl.beta == 1 &&
          !pl.recency_transposed && !pl.triangular && !pl.skip_saturated && pl.heads <= device_compute_units();
