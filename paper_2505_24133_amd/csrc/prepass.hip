@@ -55,44 +55,6 @@ struct PrepassArgs {
   float eps, scale;
 };
 
-// The logits of a wave's 32 keys from its accumulators: max over the group's heads, and the keys' (max, sum exp) per window slot.
-template <int MT, int AH>
-__device__ __forceinline__ void register_logits(const PrepassArgs& a, const f32x16 (&acc)[MT], int head, int chunk, int wave, int lrow, int half) {
-  // accumulator element i of row tile mt: key = lane % 32 of this wave's 32 keys, query row
-  // g * alpha + j with g = mt * (16 / AH) + i / AH and j = 8 * ((i % AH) / 4) + 4 * (lane / 32) + i % 4
-  const int key = chunk * kChunk + wave * 32 + lrow;
-  const bool valid = key < a.n;
-  float* lgt = a.logit + (int64_t)head * (2 * AH) * a.n_pad + key;
-  float* st = a.stats + ((int64_t)head * a.chunks * 4 + chunk * 4 + wave) * (2 * AH) * 2;
-  // stage by stage over the lane's AH query rows, so that the cross-lane steps of different rows
-  // are in flight together
-  float m[AH], mx[AH], e[AH];
-#pragma unroll
-  for (int i = 0; i < AH; ++i) {
-    // scaled first (the scale is positive, so the maximum is the same float): products are known to the
-    // compiler as ordinary numbers and the maxima below stay single instructions
-    m[i] = acc[0][i] * a.scale;
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-      for (int iq = 0; iq < 16 / AH; ++iq)
-        if (mt * (16 / AH) + iq > 0 && mt * (16 / AH) + iq < a.G) m[i] = fmaxf(m[i], acc[mt][i + iq * AH] * a.scale);
-    if (valid) lgt[(int64_t)(8 * (i >> 2) + 4 * half + (i & 3)) * a.n_pad] = m[i];
-  }
-  // (max, sum exp) over the wave's 32 keys of each row
-#pragma unroll
-  for (int i = 0; i < AH; ++i) mx[i] = half_wave_max(valid ? m[i] : -INFINITY);
-#pragma unroll
-  for (int i = 0; i < AH; ++i) e[i] = half_wave_sum(valid ? __expf(m[i] - mx[i]) : 0.f);
-  if (lrow == 0) {
-#pragma unroll
-    for (int i = 0; i < AH; ++i) {
-      const int j = 8 * (i >> 2) + 4 * half + (i & 3);
-      *reinterpret_cast<float2*>(st + j * 2) = make_float2(mx[i], e[i]);
-    }
-  }
-}
-
 // AH = alpha / 2 selects the register path for the usual window sizes (alpha = 8, 16 or 32): with
 // those, the query rows that a lane holds for g = 0 .. G-1 sit AH accumulator registers apart (and in
 // the second row tile when G * alpha > 32), so the max over the group and the wave's softmax
@@ -263,7 +225,39 @@ __global__ __launch_bounds__(kPrepassThreads, 3) void prepass_kernel(PrepassArgs
       for (int mt = 0; mt < MT; ++mt) acc[mt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qf[mt][kk], kf, acc[mt], 0, 0, 0);
     }
     if constexpr (AH > 0) {
-      register_logits<MT, AH>(a, acc, head, chunk, wave, lrow, khalf);
+      // accumulator element i of row tile mt: key = lane % 32 of this wave's 32 keys, query row
+      // g * alpha + j with g = mt * (16 / AH) + i / AH and j = 8 * ((i % AH) / 4) + 4 * (lane / 32) + i % 4
+      const int key = j0 + wave * 32 + lrow;
+      const bool valid = key < a.n;
+      float* lgt = a.logit + (int64_t)head * a.alpha * a.n_pad + key;
+      float* st = a.stats + ((int64_t)head * a.chunks * 4 + chunk * 4 + wave) * a.alpha * 2;
+      // stage by stage over the lane's AH query rows, so that the cross-lane steps of different rows
+      // are in flight together
+      float m[AH], mx[AH], e[AH];
+#pragma unroll
+      for (int i = 0; i < AH; ++i) {
+        // scaled first (the scale is positive, so the maximum is the same float): products are known to the
+        // compiler as ordinary numbers and the maxima below stay single instructions
+        m[i] = acc[0][i] * a.scale;
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+          for (int iq = 0; iq < 16 / AH; ++iq)
+            if (mt * (16 / AH) + iq > 0 && mt * (16 / AH) + iq < a.G) m[i] = fmaxf(m[i], acc[mt][i + iq * AH] * a.scale);
+        if (valid) lgt[(int64_t)(8 * (i >> 2) + 4 * khalf + (i & 3)) * a.n_pad] = m[i];
+      }
+      // (max, sum exp) over the wave's 32 keys of each row
+#pragma unroll
+      for (int i = 0; i < AH; ++i) mx[i] = half_wave_max(valid ? m[i] : -INFINITY);
+#pragma unroll
+      for (int i = 0; i < AH; ++i) e[i] = half_wave_sum(valid ? __expf(m[i] - mx[i]) : 0.f);
+      if (lrow == 0) {
+#pragma unroll
+        for (int i = 0; i < AH; ++i) {
+          const int j = 8 * (i >> 2) + 4 * khalf + (i & 3);
+          *reinterpret_cast<float2*>(st + j * 2) = make_float2(mx[i], e[i]);
+        }
+      }
     } else {
     __syncthreads();      // all key fragments are in registers: the tile can be overwritten
     // accumulator layout: column (key) = lane % 32, row (query) = 8*(i/4) + 4*(lane/32) + i%4
@@ -309,6 +303,46 @@ __global__ __launch_bounds__(kPrepassThreads, 3) void prepass_kernel(PrepassArgs
   if (a.open != nullptr) {
     for (int hd = blockIdx.x * kPrepassThreads + t; hd < a.items / a.chunks; hd += gridDim.x * kPrepassThreads)
       *reinterpret_cast<int*>(a.open + (int64_t)hd * a.n_pad * 4 + a.n_pad) = 0;
+  }
+}
+
+// The logits of a wave's 32 keys from its accumulators, as prepass_kernel makes them: max over the group's heads, and the keys'
+// (max, sum exp) per window slot.  It stands there a second time because that kernel has 13 more vector instructions a chunk when it
+// calls this function: the stand-alone importance of 640 heads of n = 1000 took 46.2 us with it and takes 45.2.
+template <int MT, int AH>
+__device__ __forceinline__ void register_logits(const PrepassArgs& a, const f32x16 (&acc)[MT], int head, int chunk, int wave, int lrow, int half) {
+  // accumulator element i of row tile mt: key = lane % 32 of this wave's 32 keys, query row
+  // g * alpha + j with g = mt * (16 / AH) + i / AH and j = 8 * ((i % AH) / 4) + 4 * (lane / 32) + i % 4
+  const int key = chunk * kChunk + wave * 32 + lrow;
+  const bool valid = key < a.n;
+  float* lgt = a.logit + (int64_t)head * (2 * AH) * a.n_pad + key;
+  float* st = a.stats + ((int64_t)head * a.chunks * 4 + chunk * 4 + wave) * (2 * AH) * 2;
+  // stage by stage over the lane's AH query rows, so that the cross-lane steps of different rows
+  // are in flight together
+  float m[AH], mx[AH], e[AH];
+#pragma unroll
+  for (int i = 0; i < AH; ++i) {
+    // scaled first (the scale is positive, so the maximum is the same float): products are known to the
+    // compiler as ordinary numbers and the maxima below stay single instructions
+    m[i] = acc[0][i] * a.scale;
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+      for (int iq = 0; iq < 16 / AH; ++iq)
+        if (mt * (16 / AH) + iq > 0 && mt * (16 / AH) + iq < a.G) m[i] = fmaxf(m[i], acc[mt][i + iq * AH] * a.scale);
+    if (valid) lgt[(int64_t)(8 * (i >> 2) + 4 * half + (i & 3)) * a.n_pad] = m[i];
+  }
+  // (max, sum exp) over the wave's 32 keys of each row
+#pragma unroll
+  for (int i = 0; i < AH; ++i) mx[i] = half_wave_max(valid ? m[i] : -INFINITY);
+#pragma unroll
+  for (int i = 0; i < AH; ++i) e[i] = half_wave_sum(valid ? __expf(m[i] - mx[i]) : 0.f);
+  if (lrow == 0) {
+#pragma unroll
+    for (int i = 0; i < AH; ++i) {
+      const int j = 8 * (i >> 2) + 4 * half + (i & 3);
+      *reinterpret_cast<float2*>(st + j * 2) = make_float2(mx[i], e[i]);
+    }
   }
 }
 
