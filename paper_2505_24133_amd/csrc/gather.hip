@@ -8,6 +8,7 @@
 // first lie between.
 #include <algorithm>
 
+#include "gather_index.h"
 #include "rkv_internal.h"
 
 namespace rkv {
@@ -18,9 +19,11 @@ typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));   // a type the 
 
 constexpr int kGatherThreads = 256;
 constexpr int kRowsPerBlock = kGatherThreads / 16;
-// A launch takes fewer than 2^32 work items in a dimension.  Calls with more blocks are made in several launches, up to the number of
-// rows that one launch of 64 rows a block takes (2^30, 512 GB of outputs).
-constexpr int64_t kMaxBlocks = (1ll << 32) / kGatherThreads - 1;
+// A launch takes fewer than 2^32 work items in a dimension.  Calls with more blocks are made in several launches, each of a multiple
+// of 8 workgroups so that the next one's begin at the same XCD, up to the number of rows that one launch of 64 rows a block takes (2^30,
+// 512 GB of outputs).
+constexpr int64_t kMaxBlocks = (1ll << 32) / kGatherThreads - 8;
+constexpr int64_t kMaxBlocksOf64 = (1ll << 32) / kGatherThreads - 1;
 
 struct GatherArgs {
   const uint16_t* k;
@@ -28,7 +31,8 @@ struct GatherArgs {
   const int32_t* kept;
   uint16_t* k_out;
   uint16_t* v_out;
-  int H, N, budget, blocks_per_head;
+  int heads, H, N, budget;
+  uint32_t blocks_per_head, eights, run, step;
   uint32_t first;              // block of the whole call that this launch begins with
   KvLayout kl, vl;
   int64_t osp, osh, ost;
@@ -36,9 +40,9 @@ struct GatherArgs {
 
 template <bool PAGED, bool STREAM>
 __global__ __launch_bounds__(kGatherThreads) void gather_kernel(GatherArgs a) {
-  const uint32_t block = a.first + blockIdx.x;
-  const int head = (int)(block / (uint32_t)a.blocks_per_head);
-  const int blk = (int)block - head * a.blocks_per_head;
+  int head, blk;
+  gather_piece(a.first + blockIdx.x, a.blocks_per_head, a.eights, a.run, a.step, head, blk);
+  if (head >= a.heads) return;
   const int p = head / a.H;
   const int h = head - p * a.H;
   const int c16 = threadIdx.x & 15;
@@ -64,13 +68,15 @@ __global__ __launch_bounds__(kGatherThreads) void gather_kernel(GatherArgs a) {
   __builtin_nontemporal_store(vr, reinterpret_cast<u32x4*>(a.v_out + o));
 }
 
+int64_t cache_bytes(const Plan& pl) { return (int64_t)pl.heads * pl.N * kRowBytes * 2; }     // K and V
+
 // Caches that the 256 MB behind the L2s cannot hold are read past it: the pre-pass's keys are gone from there and nothing reads these
 // rows again.  K and V, us, ordinary / non-temporal loads, behind the other kernels of an attention-only step: 180 MiB 83 / 88, 252 114 / 116,
 // 288 127 / 129, 325 170 / 170, 360 168 / 164, paged (a dense copy of the keys is in the way, too) 180 106 / 104, 252 148 / 140, 288 168 / 159,
 // 360 225 / 210; a whole step of 256 heads of n = 4216 (1.1 GB) 431 / 406, of 256 MB paged 240 / 230, of 6144 heads of n = 2168 (6.8 GB)
 // 4749 / 4657, of 1024 of n = 8312 3131 / 3081.  Between 256 and 330 MiB a contiguous cache would still do better from there, by 1 % of a step
 // and a tenth of the gather by itself.
-bool gather_streams(const Plan& pl) { return (int64_t)pl.heads * pl.N * kRowBytes * 2 > (256ll << 20); }
+bool gather_streams(const Plan& pl) { return cache_bytes(pl) > (256ll << 20); }
 
 }  // namespace
 
@@ -82,17 +88,18 @@ hipError_t launch_gather(const Plan& pl, const void* k, const void* v, const int
   a.kept = kept_idx;
   a.k_out = static_cast<uint16_t*>(k_out);
   a.v_out = static_cast<uint16_t*>(v_out);
-  a.H = pl.H; a.N = pl.N; a.budget = pl.budget;
-  a.blocks_per_head = (int)(((int64_t)pl.budget + kRowsPerBlock - 1) / kRowsPerBlock);
+  a.heads = pl.heads; a.H = pl.H; a.N = pl.N; a.budget = pl.budget;
+  a.blocks_per_head = (uint32_t)(((int64_t)pl.budget + kRowsPerBlock - 1) / kRowsPerBlock);
   a.kl = k_layout(pl); a.vl = v_layout(pl);
   a.osp = pl.osp; a.osh = pl.osh; a.ost = pl.ost;
-  if (pl.heads * (((int64_t)pl.budget + 63) / 64) > kMaxBlocks) return hipErrorInvalidConfiguration;
-  const int64_t blocks = (int64_t)pl.heads * a.blocks_per_head;
+  if (pl.heads * (((int64_t)pl.budget + 63) / 64) > kMaxBlocksOf64) return hipErrorInvalidConfiguration;
+  const GatherOrder order = gather_order(pl.heads, a.blocks_per_head, cache_bytes(pl));
+  a.eights = order.eights; a.run = order.run; a.step = order.step;
   auto launch = [&](auto kernel) {
     hipError_t e = hipSuccess;
-    for (int64_t first = 0; first < blocks && e == hipSuccess; first += kMaxBlocks) {
+    for (int64_t first = 0; first < order.blocks && e == hipSuccess; first += kMaxBlocks) {
       a.first = (uint32_t)first;
-      hipLaunchKernelGGL(kernel, dim3((unsigned)std::min(blocks - first, kMaxBlocks)), dim3(kGatherThreads), 0, stream, a);
+      hipLaunchKernelGGL(kernel, dim3((unsigned)std::min(order.blocks - first, kMaxBlocks)), dim3(kGatherThreads), 0, stream, a);
       e = hipGetLastError();
     }
     return e;

@@ -1,4 +1,5 @@
-"""The launches of the gather of kept rows: none holds more work items than the runtime takes, and calls that need more than one are whole."""
+"""The launches of the gather of kept rows: none holds more work items than the runtime takes, calls that need more than one are whole, and
+a head's rows are moved by one XCD, or by few."""
 import os
 import subprocess
 
@@ -34,13 +35,68 @@ def test_every_launch_is_one_the_runtime_takes(recorder, P, H, N, budget, page, 
     r = subprocess.run([recorder, *map(str, (P, H, N, budget, page))], capture_output=True, text=True)
     assert r.returncode == 0, r.stdout + r.stderr
     word = r.stdout.split()
-    assert [int(word[1]), int(word[3]), int(word[5])] == [rkv.RKV_OK, launches, P * H * -(-budget // 16)], r.stdout
+    assert [int(word[1]), int(word[3]), int(word[5])] == [rkv.RKV_OK, launches, -(-P * H * -(-budget // 16) // 8) * 8], r.stdout
     assert int(word[7]) * 256 < 1 << 32
 
 
 def test_what_was_too_large_stays_refused(recorder):
     r = subprocess.run([recorder, str(1 << 19), "8", "400", "256", "0"], capture_output=True, text=True)
     assert r.stdout.startswith(f"status {rkv.RKV_ERR_HIP} launches 0 "), r.stdout
+
+
+@pytest.fixture(scope="module")
+def order_check(repo_root, tmp_path_factory):
+    exe = str(tmp_path_factory.mktemp("order") / "gather_order_check")
+    subprocess.run(["g++", "-O1", "-Wall", "-I", os.path.join(repo_root, "paper_2505_24133_amd", "csrc"),
+                    os.path.join(repo_root, "tests", "gather_order_check.cpp"), "-o", exe], check=True)
+    return exe
+
+
+@pytest.mark.parametrize("heads", [1, 3, 7, 8, 9, 20, 256])
+@pytest.mark.parametrize("per", [1, 7, 65, 640, 641, 2024])
+@pytest.mark.parametrize("launch", [64, 1 << 24])
+@pytest.mark.parametrize("cache_bytes", [0, (256 << 20) - 1, 256 << 20])
+def test_every_block_is_taken_once(order_check, heads, per, launch, cache_bytes):
+    r = subprocess.run([order_check, *map(str, (heads, per, launch, cache_bytes))], capture_output=True, text=True)
+    assert r.stdout == "ok" and r.returncode == 0, r.stdout
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("page", [0, 16])
+@pytest.mark.parametrize("P,H", [(1, 1), (3, 3), (2, 8), (3, 4)])
+@pytest.mark.parametrize("budget", [17, 385])
+def test_rows_of_every_head(P, H, budget, page):
+    n_tokens = 400
+    print(f"[gpu-case] gather P={P} H={H} budget={budget} page={page}", flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(4)
+    k, v = (torch.randn((P, H, n_tokens, 128), generator=gen, device="cuda").bfloat16() for _ in range(2))
+    kept = torch.randint(0, n_tokens, (P, H, budget), generator=gen, device="cuda", dtype=torch.int32)
+    want = [torch.gather(x, 2, kept.long()[..., None].expand(-1, -1, -1, 128)) for x in (k, v)]
+    shape = rkv.Shape(num_problems=P, kv_heads=H, q_heads=H, n_tokens=n_tokens, budget=budget, alpha=1)
+    if page:
+        per = n_tokens // page
+        shape.page_size, shape.block_table = page, torch.randperm(P * per, generator=gen, device="cuda").int().reshape(P, per)
+        pools = [torch.empty((P * per, H, page, 128), dtype=torch.bfloat16, device="cuda") for _ in range(2)]
+        for pool, x in zip(pools, (k, v)):
+            pool[shape.block_table.long()] = x.reshape(P, H, per, page, 128).transpose(1, 2)
+        k, v = pools
+    out = [torch.full((P, H, budget, 128), 7.0, dtype=torch.bfloat16, device="cuda") for _ in range(2)]
+    rkv.rkv_compact(shape, k, v, kept, k_out=out[0], v_out=out[1])
+    assert torch.equal(out[0], want[0]) and torch.equal(out[1], want[1])
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("budget", [10240, 10241, 32700])
+def test_rows_of_long_lists(budget):
+    """17 heads of 32768 tokens, 272 MiB: below and beyond the length where the order of the blocks changes."""
+    heads, n_tokens = 17, 32768
+    print(f"[gpu-case] gather heads={heads} n_tokens={n_tokens} budget={budget}", flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(6)
+    k, v = (torch.randn((1, heads, n_tokens, 128), generator=gen, device="cuda").bfloat16() for _ in range(2))
+    kept = torch.randint(0, n_tokens, (1, heads, budget), generator=gen, device="cuda", dtype=torch.int32)
+    shape = rkv.Shape(num_problems=1, kv_heads=heads, q_heads=heads, n_tokens=n_tokens, budget=budget)
+    for x, got in zip((k, v), rkv.rkv_compact(shape, k, v, kept)):
+        assert torch.equal(got, torch.gather(x, 2, kept.long()[..., None].expand(-1, -1, -1, 128)))
 
 
 @pytest.mark.gpu
