@@ -68,16 +68,6 @@ __global__ __launch_bounds__(kGatherThreads) void gather_kernel(GatherArgs a) {
   __builtin_nontemporal_store(vr, reinterpret_cast<u32x4*>(a.v_out + o));
 }
 
-int64_t cache_bytes(const Plan& pl) { return (int64_t)pl.heads * pl.N * kRowBytes * 2; }     // K and V
-
-// Caches that the 256 MB behind the L2s cannot hold are read past it: the pre-pass's keys are gone from there and nothing reads these
-// rows again.  K and V, us, ordinary / non-temporal loads, behind the other kernels of an attention-only step: 180 MiB 83 / 88, 252 114 / 116,
-// 288 127 / 129, 325 170 / 170, 360 168 / 164, paged (a dense copy of the keys is in the way, too) 180 106 / 104, 252 148 / 140, 288 168 / 159,
-// 360 225 / 210; a whole step of 256 heads of n = 4216 (1.1 GB) 431 / 406, of 256 MB paged 240 / 230, of 6144 heads of n = 2168 (6.8 GB)
-// 4749 / 4657, of 1024 of n = 8312 3131 / 3081.  Between 256 and 330 MiB a contiguous cache would still do better from there, by 1 % of a step
-// and a tenth of the gather by itself.
-bool gather_streams(const Plan& pl) { return cache_bytes(pl) > (256ll << 20); }
-
 }  // namespace
 
 hipError_t launch_gather(const Plan& pl, const void* k, const void* v, const int32_t* kept_idx,
@@ -93,7 +83,7 @@ hipError_t launch_gather(const Plan& pl, const void* k, const void* v, const int
   a.kl = k_layout(pl); a.vl = v_layout(pl);
   a.osp = pl.osp; a.osh = pl.osh; a.ost = pl.ost;
   if (pl.heads * (((int64_t)pl.budget + 63) / 64) > kMaxBlocksOf64) return hipErrorInvalidConfiguration;
-  const GatherOrder order = gather_order(pl.heads, a.blocks_per_head, cache_bytes(pl));
+  const GatherOrder order = gather_order(pl.heads, a.blocks_per_head, gather_cache_bytes(pl.heads, pl.N));
   a.eights = order.eights; a.run = order.run; a.step = order.step;
   auto launch = [&](auto kernel) {
     hipError_t e = hipSuccess;
@@ -104,7 +94,7 @@ hipError_t launch_gather(const Plan& pl, const void* k, const void* v, const int
     }
     return e;
   };
-  if (gather_streams(pl)) return launch(pl.paged ? gather_kernel<true, true> : gather_kernel<false, true>);
+  if (gather_streams(pl.heads, pl.N, pl.budget, pl.paged)) return launch(pl.paged ? gather_kernel<true, true> : gather_kernel<false, true>);
   return launch(pl.paged ? gather_kernel<true, false> : gather_kernel<false, false>);
 }
 

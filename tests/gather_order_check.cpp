@@ -2,6 +2,7 @@
 // are dealt to them in turn) get whole heads, and of up to seven heads that are left one run each.
 // Long lists of large caches go to the XCDs block by block.
 // Usage: gather_order_check heads blocks_per_head launch (workgroups a launch takes) cache_bytes.  Prints "ok" or what is wrong.
+// gather_order_check streams heads n_tokens budget paged: whether the rows are read past the caches, 1 or 0.
 #include <cstdio>
 #include <cstdlib>
 #include <vector>
@@ -9,6 +10,7 @@
 #include "gather_index.h"
 
 int main(int argc, char** argv) {
+  if (argc == 6) return std::printf("%d", rkv::gather_streams(std::atoi(argv[2]), std::atoi(argv[3]), std::atoi(argv[4]), std::atoi(argv[5]) != 0) ? 1 : 0), 0;
   if (argc != 5) return 2;
   const int64_t heads = std::atoll(argv[1]), per = std::atoll(argv[2]), launch = std::atoll(argv[3]);
   const int64_t bytes = std::atoll(argv[4]);

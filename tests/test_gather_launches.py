@@ -61,6 +61,17 @@ def test_every_block_is_taken_once(order_check, heads, per, launch, cache_bytes)
     assert r.stdout == "ok" and r.returncode == 0, r.stdout
 
 
+@pytest.mark.parametrize("heads,n_tokens,budget,paged,streams", [
+    (256, 2048, 2048, 0, 0), (257, 2048, 2048, 0, 1), (256, 2049, 2049, 0, 1),
+    (256, 4224, 410, 0, 0), (512, 1152, 576, 0, 0), (256, 2176, 1632, 0, 0), (256, 4224, 2049, 0, 1),
+    (256, 2048, 8000, 0, 0), (256, 2049, 8000, 0, 1),
+    (256, 2048, 16, 1, 0), (256, 2049, 16, 1, 1), (256, 2176, 2048, 1, 1),
+])
+def test_rows_read_past_the_caches(order_check, heads, n_tokens, budget, paged, streams):
+    r = subprocess.run([order_check, "streams", *map(str, (heads, n_tokens, budget, paged))], capture_output=True, text=True)
+    assert r.stdout == str(streams)
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("page", [0, 16])
 @pytest.mark.parametrize("P,H", [(1, 1), (3, 3), (2, 8), (3, 4)])
