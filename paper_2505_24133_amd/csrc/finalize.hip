@@ -468,6 +468,16 @@ __global__ __launch_bounds__(kFinThreads, PLAIN == 2 ? 8 : 4) void finalize_kern
       else keys[i] = order_key(z);
     }
   };
+  if constexpr (MODE == kModeSelect) {
+    // (the same by itself: through the functions above its addresses take vector registers, 1600 heads of n = 100 14.75 us instead of 14.4)
+    for (int i = t; i < n; i += kFinThreads) {
+      const float imp = a.imp_in[(int64_t)head * n + i];
+      const float rd = a.red_in ? a.red_in[(int64_t)head * n + i] : 0.f;
+      const float z = a.lambda * imp - (1.0f - a.lambda) * rd;
+      if (a.score_out) a.score_out[(int64_t)head * n + i] = z;
+      keys[i] = order_key(z);
+    }
+  } else
   for (int i0 = t; i0 < n; i0 += BATCH * kFinThreads) {
     float imp[BATCH], sim[BATCH];
 #pragma unroll

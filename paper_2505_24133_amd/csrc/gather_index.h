@@ -26,7 +26,8 @@ RKV_HD int64_t gather_cache_bytes(int64_t heads, int64_t rows) { return heads * 
 // Rows that the 256 MB behind the L2s cannot hold are read past them: the pre-pass's keys are gone from there and nothing reads these
 // rows again.  Of contiguous caches the rows that are read count: with all of the cache's counted, a tenth kept of 256 heads of n = 4216 took
 // 20.3 us instead of 17.4, half of 512 of 1144 49.9 instead of 44.0, three quarters of 256 of 2168 70.6 instead of 60.3.
-// Paged ones count whole, since a dense copy of the keys is in the way, too: a step of 256 of n = 2168 240 / 230.  K and V, us, ordinary / non-temporal loads, behind the other kernels of an attention-only step: 180 MiB 83 / 88, 252 114 / 116,
+// Paged ones count whole, since a dense copy of the keys is in the way, too: a step of 256 of n = 2168 240 / 230.
+// K and V, us, ordinary / non-temporal loads, behind the other kernels of an attention-only step: 180 MiB 83 / 88, 252 114 / 116,
 // 288 127 / 129, 325 170 / 170, 360 168 / 164, paged 180 106 / 104, 252 148 / 140, 288 168 / 159, 360 225 / 210; a whole step of 256 heads of
 // n = 4216 (1.1 GB) 431 / 406, of 6144 heads of n = 2168 (6.8 GB) 4749 / 4657, of 1024 of n = 8312 3131 / 3081.
 RKV_HD bool gather_streams(int64_t heads, int64_t n_tokens, int64_t budget, bool paged) {
